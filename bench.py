@@ -97,7 +97,7 @@ class Single:
 
     def run(self, steps, warmup, pass_reps, adjoint_steps, K, copy_ceiling=True):
         import torch
-        from paper_2603_25282_amd.sgp import SGP_PASS_X, SGP_PASS_Y, SGP_PASS_YINV, SGP_PASS_Z, SgpError
+        from paper_2603_25282_amd.sgp import SGP_PASS_X, SGP_PASS_Y, SGP_PASS_Z, SgpError
         cfg, s = self.cfg, self.s
         npts, esz = cfg.points, self.esz
         psi = self.dev()
@@ -108,7 +108,7 @@ class Single:
         # Measured before the timed region, so that the GPU is busy up to it.
         scratch = psi.clone()
         passes = {"xpass": SGP_PASS_X, "ypass": SGP_PASS_Y} if cfg.dim == 2 else \
-            {"xpass": SGP_PASS_X, "ypass_fwd": SGP_PASS_Y, "zpass": SGP_PASS_Z, "ypass_inv": SGP_PASS_YINV}
+            {"xpass": SGP_PASS_X, "ypass": SGP_PASS_Y, "zpass": SGP_PASS_Z}
         pair, iso = {}, {}
         for name, pk in passes.items():
             s.time_pass(scratch, pk, 4, in_steps=True)
@@ -162,12 +162,11 @@ class Single:
         # event-timed step split by the passes' shares, per launch
         # algorithmic bytes per grid point per launch: read + write 5 components, plus
         # the (C - 1, S) propagator table (2 reals per (x, y) wavevector) on the pass
-        # that applies it: the 2D y-pass reads each entry once; the 3D forward y-pass
-        # reads the N^2-entry table once per z-plane, from L2 after the first plane,
-        # so its HBM share is nz times smaller and left out
-        table_b = 2 * esz // 2
-        per_point = {"xpass": 2 * 5 * esz, "ypass": 2 * 5 * esz + table_b,
-                     "ypass_fwd": 2 * 5 * esz, "zpass": 2 * 5 * esz, "ypass_inv": 2 * 5 * esz}
+        # that applies it: the 2D y-pass reads each entry once; the 3D y-pass reads the
+        # N^2-entry table once per z-plane, from L2 after the first plane, so its HBM
+        # share is nz times smaller and left out
+        table_b = 2 * esz // 2 if cfg.dim == 2 else 0
+        per_point = {"xpass": 2 * 5 * esz, "ypass": 2 * 5 * esz + table_b, "zpass": 2 * 5 * esz}
         lps = 3 if cfg.order == 4 else 1  # launches of each pass per step (merged nonlinear substeps)
         step_ms = region_ms / steps
         tot = sum(pair[k] * lps for k in passes)
@@ -271,11 +270,7 @@ def stored_traffic(name, dtype, kernel, plan):
     try:
         tr = json.load(open(tpath))
         key = f"{name}:{dtype}:{kernel}"
-        # the 3D forward y-pass and z-pass kernels also depend on the linear
-        # substep's split (the plan's fourth entry): one entry per split
-        if kernel in ("ypass_fwd", "zpass") and len(plan) > 3:
-            key += f":split{plan[3]}"
-        ax = {"xpass": 0, "ypass": 1, "ypass_fwd": 1, "ypass_inv": 1, "zpass": 2}[kernel]
+        ax = {"xpass": 0, "ypass": 1, "zpass": 2}[kernel]
         if key in tr and tr[key].get("source_hash") == source_hash() and tr[key].get("plan")[ax] == plan[ax]:
             return tr[key]["bytes_per_launch"]
     except Exception:

@@ -187,7 +187,7 @@ int sgp_store_size(const sgp_ctx* ctx, long nsteps, size_t* bytes);
 /* sgp_step() that also writes, for every pass, the input of its pointwise stage
  * into the caller-owned device buffer `store` (slot 2k: the k-th nonlinear
  * substep's input in physical space; slot 2k+1: the k-th propagator's input in
- * Fourier space).  No graph replay.  Advances the clock like sgp_step(). */
+ * Fourier space, in 3D in (nu_p, nu_q) per z-plane).  No graph replay.  Advances the clock like sgp_step(). */
 int sgp_step_store(sgp_ctx* ctx, void* psi_dev, long nsteps, void* store, size_t store_bytes);
 
 /* Reverse sweep of the sgp_step_store(nsteps) call that started at the current
@@ -210,10 +210,11 @@ int sgp_set_time(sgp_ctx* ctx, double t);
  * launched `reps` times back to back on the context stream between two HIP
  * events (the state is overwritten with transformed data).  pass: 0 = X-pass
  * (inverse FFT along x, nonlinear flow, forward FFT; the nonlinear flow of
- * Sec. 3.2); 1 = y-pass (2D: FFT along y, propagator, inverse FFT; 3D: forward
- * FFT along y); 2 = z-pass with the propagator (3D); 3 = inverse y-pass (3D).
+ * Sec. 3.2); 1 = y-pass (FFT along y, propagator in (nu_p, nu_q), inverse FFT);
+ * 2 = z-pass (3D: FFT along z, z kinetic phase, inverse FFT); 3 = the pass that holds
+ * the inverse FFT along y (3D), which is the y-pass.
  * With pass | SGP_TIME_IN_STEP the passes of a substep run in step order (2D:
- * y, X; 3D: y, z, inverse y, X) `reps` times and only the launches of the named
+ * y, X; 3D: y, z, X) `reps` times and only the launches of the named
  * pass are timed, each between its own pair of events (its data then comes from
  * the previous pass, as inside sgp_step).  With pass | SGP_TIME_STEPS, `reps` (>= 2)
  * whole steps of sgp_step's schedule run (launched without the graph; psi
@@ -244,18 +245,17 @@ int sgp_time_pass(sgp_ctx* ctx, void* psi_dev, int pass, int reps, double* avg_m
  *   and drops the captured step graph; call it between steps, not concurrently
  *   with work on the context's stream.
  * sgp_get_plan: the current width of `axis`.
- * Pseudo-axis SGP_PLAN_LINEAR (3D contexts only; SGP_ERR_ARG otherwise): how a
- *   linear substep's passes split the propagator of eq. sl1, whose spin part
- *   exp(i d Q) depends on (nu_p, nu_q) only (Sec. 3.1, 3D): 0 (default) = FFT
- *   along y, then along z the FFT, the whole propagator and the inverse FFT, then
- *   the inverse FFT along y; 1 = FFT along y with the x and y kinetic phases and
- *   the spin part applied there, then along z the FFT, the z kinetic phase and the
- *   inverse FFT, then the inverse FFT along y.  Same results up to rounding; with
- *   sgp_set_plan(ctx, SGP_PLAN_LINEAR, 0 or 1) and sgp_get_plan likewise.  The
- *   differentiable path (sgp_step_store, the adjoint) always uses split 0.
+ * Pseudo-axis SGP_PLAN_LINEAR (3D contexts only; SGP_ERR_ARG otherwise): the order of
+ *   a linear substep's two passes.  The propagator of eq. sl1 is the product of its part
+ *   in (nu_p, nu_q) (spin part exp(i d Q) and in-plane kinetic phase; Sec. 3.1, 3D) and
+ *   the z kinetic phase, which commute: 0 (default) = the y-pass (FFT along y, the
+ *   former, inverse FFT), then the z-pass (FFT along z, the latter, inverse FFT); 1 = the
+ *   z-pass first.  Same results up to rounding; with sgp_set_plan(ctx, SGP_PLAN_LINEAR,
+ *   0 or 1) and sgp_get_plan likewise.  The differentiable path (sgp_step_store, the
+ *   adjoint) always uses order 0.
  * sgp_autotune: picks the fastest combination of the axes' widths (every
  *   combination, at most 9 in 2D and 27 in 3D, in 3D for both linear-substep
- *   splits) by timing `steps` steps of the
+ *   orders) by timing `steps` steps of the
  *   sgp_step path for each, after one untimed call of `steps` steps; psi_dev is
  *   a device state in the layout of sgp_step; it is advanced by every timed and
  *   untimed step (pass a scratch copy).  Needs the workspace and the propagator;
@@ -273,11 +273,10 @@ int sgp_autotune(sgp_ctx* ctx, void* psi_dev, int steps, int elems_out[3], doubl
  * from a captured HIP graph (value 0 launches every kernel individually). */
 enum { SGP_OPT_GRAPH = 1, SGP_OPT_BATCHED = 2, SGP_OPT_FRAME = 3, SGP_OPT_SLABS = 4 };
 /* SGP_OPT_SLABS (3D contexts; default 0 = off): S >= 2 z-slabs, S dividing nz.  With
- * the graph replay and the linear-substep split 0, the passes of a step that act on
- * each z-plane alone (the inverse y-pass, the x-pass, the next forward y-pass; Sec.
- * 3.1's 3D step) run slab by slab between two z-passes, alternate slabs on a second
- * stream, so that the bandwidth-bound y-passes of one slab overlap the x-pass of
- * another.  Bitwise the same results.  SGP_ERR_ARG for a 2D context or an S that does
+ * the graph replay and the linear-substep order 0, the passes of a step that act on
+ * each z-plane alone (the x-pass and the next y-pass; Sec. 3.1's 3D step) run slab by
+ * slab between two z-passes, alternate slabs on a second stream, so that the y-pass of
+ * one slab overlaps the x-pass of another.  Bitwise the same results.  SGP_ERR_ARG for a 2D context or an S that does
  * not divide nz; 0 or 1 switches it off. */
 /* SGP_OPT_FRAME: SGP_FRAME_ROTATING (default) evolves Phi in the rotating frame
  * (trap at R(Omega s) x, merged nonlinear substeps, graph replay); SGP_FRAME_LAB runs

@@ -99,8 +99,8 @@ struct sgp_ctx {
 
   // register plan width E of the passes along each axis
   int plan_e[3] = {0, 0, 0};
-  // 3D linear substep: 0 = FFT y, whole propagator in the z-pass, iFFT y (default);
-  // 1 = FFT y with the spin part in the y-pass, z kinetic phase in the z-pass, iFFT y
+  // 3D linear substep: 0 = y-pass (in-plane part of the propagator), then z-pass (z
+  // kinetic phase) (default); 1 = z-pass, then y-pass
   int lin_split = 0;
   // 0: evolve Phi in the rotating frame (default); 1: Algorithm 1 literally (lab frame)
   int frame = 0;
@@ -121,8 +121,7 @@ struct sgp_ctx {
   hipGraphExec_t gexec[kGraphLevels] = {};
   void* gpsi = nullptr;
   bool use_graph = true;
-  // 3D, split 0: the graph body runs its z-local passes (inverse y, X, forward y)
-  // per z-slab, the slabs alternating between two streams (0: off)
+  // 3D, split 0: the graph body runs its z-local passes (X, y) per z-slab, the slabs alternating between two streams (0: off)
   int slabs = 0;
   hipStream_t cap2 = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};
@@ -246,6 +245,17 @@ void column_geometry(const sgp_ctx* c, int axis, PassArgs& a) {
   a.nu_scale_l = kPi / c->g.L[axis];
 }
 
+// Propagator tables of one linear substep length for lines along `axis`.
+void propagator_tables(const sgp_ctx* c, int table, int axis, PassArgs& a) {
+  a.cs = c->at(c->off_cs[table]);
+  a.kin_a = c->at(c->off_kin[table][0]);
+  a.kin_l = c->at(c->off_kin[table][axis]);
+}
+
+// The pass of a linear substep that advances the device clock: in 3D the z-pass, so that
+// with z-slabs no slab's y-pass moves the clock under another slab's X-pass.
+int advances_clock(const sgp_ctx* c, int kind) { return kind == (c->g.dim == 2 ? C_PROP : C_KIN); }
+
 template <typename T>
 hipError_t run_xpass(sgp_ctx* c, hipStream_t st, int mode, void* psi, double d, int clock_mode, double s_arg,
                      const hipEvent_t* ev = nullptr) {
@@ -264,19 +274,10 @@ hipError_t run_colpass(sgp_ctx* c, hipStream_t st, int mode, int axis, void* psi
                        const hipEvent_t* ev = nullptr) {
   PassArgs a = base_args(c);
   column_geometry(c, axis, a);
-  a.cs = c->at(c->off_cs[table]);
-  a.kin_a = c->at(c->off_kin[table][0]);
-  a.kin_o = c->at(c->off_kin[table][1]);
-  a.kin_l = c->at(c->off_kin[table][axis]);
+  propagator_tables(c, table, axis, a);
   a.d = d;
-  a.advance_clock = (mode == C_PROP || mode == C_FSPIN) ? 1 : 0;
-  if (!ev) {
-    int pid = -1;
-    if (axis == 1 && (mode == C_PROP || mode == C_FWD || mode == C_FSPIN)) pid = 1;
-    else if (axis == 2 && (mode == C_PROP || mode == C_KIN)) pid = 2;
-    else if (axis == 1 && mode == C_INV) pid = 3;
-    ev = timing_events(c, pid);
-  }
+  a.advance_clock = advances_clock(c, mode);
+  if (!ev) ev = timing_events(c, axis);
   return launch_pass<T>(mode, psi, a, c->g.n[axis], c->elems(axis), st, ev);
 }
 
@@ -298,36 +299,30 @@ hipError_t run_xpass_ex(sgp_ctx* c, int kind, void* psi, double d, int clock_mod
 
 template <typename T>
 hipError_t run_colpass_ex(sgp_ctx* c, int kind, int axis, void* psi, int table, double d, void* store,
-                          const void* fwd) {
+                          const void* fwd, bool adj = false) {
   PassArgs a = base_args(c);
   column_geometry(c, axis, a);
-  a.cs = c->at(c->off_cs[table]);
-  a.kin_a = c->at(c->off_kin[table][0]);
-  a.kin_o = c->at(c->off_kin[table][1]);
-  a.kin_l = c->at(c->off_kin[table][axis]);
+  propagator_tables(c, table, axis, a);
   a.d = d;
-  a.advance_clock = (kind == C_PROP) ? 1 : 0;
+  a.advance_clock = !adj && advances_clock(c, kind);
+  a.kin_conj = adj;
   a.store = store;
   a.fwd = fwd;
   a.gacc = (double*)c->at(c->off_gacc);
   return launch_pass<T>(kind, psi, a, c->g.n[axis], c->elems(axis), c->st);
 }
 
-// One exact linear substep on x-transformed data: 2D Y-pass; 3D Y1 (FFT along y, the
-// spin part of the propagator exp(i d Q(nu_p, nu_q)) with the x and y kinetic phases
-// and 1/N^3), Z (FFT along z, the z kinetic phase, inverse FFT) and Y2 (inverse FFT
-// along y).  The spin part depends on (nu_p, nu_q) only (Sec. 3.1, 3D remark), so it
-// commutes with the z transform and runs in the y-pass, whose memory time leaves
-// room for it; the z-pass then works per component.  (The differentiable path,
-// sgp_step_store and the adjoint, keeps the whole propagator in the z-pass.)
+// One exact linear substep on x-transformed data: the y-pass (FFT along y, spin part
+// exp(i d Q(nu_p, nu_q)) of the propagator with the x and y kinetic phases and 1/N^d,
+// inverse FFT) and in 3D the z-pass (FFT along z, z kinetic phase, inverse FFT).  The two
+// act on different axes and commute; lin_split is their order.
 template <typename T>
 hipError_t run_linear(sgp_ctx* c, hipStream_t st, void* psi, int table, double d) {
   if (c->g.dim == 2) return run_colpass<T>(c, st, C_PROP, 1, psi, table, d);
-  hipError_t e = run_colpass<T>(c, st, c->lin_split ? C_FSPIN : C_FWD, 1, psi, table, d);
+  const int first = c->lin_split ? 2 : 1;
+  hipError_t e = run_colpass<T>(c, st, first == 1 ? C_PROP : C_KIN, first, psi, table, d);
   if (e != hipSuccess) return e;
-  e = run_colpass<T>(c, st, c->lin_split ? C_KIN : C_PROP, 2, psi, table, d);
-  if (e != hipSuccess) return e;
-  return run_colpass<T>(c, st, C_INV, 1, psi, table, d);
+  return run_colpass<T>(c, st, first == 1 ? C_KIN : C_PROP, 3 - first, psi, table, d);
 }
 
 // One step of a composition (Sec. 3.3): nonlinear flows A[j] tau and linear flows
@@ -416,11 +411,11 @@ hipError_t enqueue_body(sgp_ctx* c, hipStream_t st, void* psi, int nbody) {
 }
 
 // One z-local pass over the planes [z0, z1) of a 3D state: the x-pass (X_MID, the
-// clock on the device) or a y-pass transform (C_FWD / C_INV).  A z-slab is a
-// contiguous part of the state, so the pass runs on it as on a grid of z1 - z0
-// planes; only the x-pass's trap potential needs the planes' position (z0).
+// clock on the device) or the y-pass (C_PROP).  A z-slab is a contiguous part of the
+// state, so the pass runs on it as on a grid of z1 - z0 planes; only the x-pass's trap
+// potential needs the planes' position (z0).
 template <typename T>
-hipError_t run_slab_pass(sgp_ctx* c, hipStream_t st, int kind, void* psi, int z0, int z1, double d) {
+hipError_t run_slab_pass(sgp_ctx* c, hipStream_t st, int kind, void* psi, int z0, int z1, int table, double d) {
   PassArgs a = base_args(c);
   const int nx = c->g.n[0], ny = c->g.n[1];
   void* p = (char*)psi + (size_t)z0 * ny * nx * 5 * 2 * c->esize;
@@ -434,16 +429,16 @@ hipError_t run_slab_pass(sgp_ctx* c, hipStream_t st, int kind, void* psi, int z0
     return launch_pass<T>(kind, p, a, nx, c->elems(0), st, nullptr);
   }
   column_geometry(c, 1, a);
+  propagator_tables(c, table, 1, a);
   a.nouter = z1 - z0;
   return launch_pass<T>(kind, p, a, ny, c->elems(1), st, nullptr);
 }
 
-// enqueue_body with the z-local passes in z-slabs (3D, split 0): the inverse y-pass,
-// the x-pass and the next forward y-pass act on each z-plane alone, so between two
-// z-passes they run slab by slab, even slabs on st and odd ones on st2 (started one
-// inverse y-pass later), and the bandwidth-bound y-passes of one slab overlap the
-// VALU-bound x-pass of another.  The same kernels as enqueue_body on the same
-// lines: bitwise the same result.
+// enqueue_body with the z-local passes in z-slabs (3D, split 0): the x-pass and the next
+// y-pass act on each z-plane alone, so between two z-passes they run slab by slab, even
+// slabs on st and odd ones on st2, and the y-pass of one slab overlaps the VALU-bound
+// x-pass of another.  The same kernels as enqueue_body on the same lines: bitwise the
+// same result.
 template <typename T>
 hipError_t enqueue_body_slabs(sgp_ctx* c, hipStream_t st, hipStream_t st2, void* psi, int nbody) {
   std::vector<double> nl, lin;
@@ -451,22 +446,20 @@ hipError_t enqueue_body_slabs(sgp_ctx* c, hipStream_t st, hipStream_t st2, void*
   schedule(c, 2, nl, lin, tab);
   const size_t per = lin.size() / 2;
   const int S = c->slabs, dz = c->g.n[2] / S;
-  hipError_t e = run_colpass<T>(c, st, C_FWD, 1, psi, tab[per], lin[per]);
+  hipError_t e = run_colpass<T>(c, st, C_PROP, 1, psi, tab[per], lin[per]);
   for (int b = 0; b < nbody && e == hipSuccess; ++b)
     for (size_t k = per; k < 2 * per && e == hipSuccess; ++k) {
-      e = run_colpass<T>(c, st, C_PROP, 2, psi, tab[k], lin[k]);
+      e = run_colpass<T>(c, st, C_KIN, 2, psi, tab[k], lin[k]);
       const double d = (k + 1 == 2 * per) ? nl[per] : nl[k + 1];
-      const bool fwd_next = !(b + 1 == nbody && k + 1 == 2 * per);
+      const bool y_next = !(b + 1 == nbody && k + 1 == 2 * per);
+      const size_t kn = k + 1 == 2 * per ? per : k + 1;
+      if (e == hipSuccess) e = hipEventRecord(c->pev[0], st);  // fork
+      if (e == hipSuccess) e = hipStreamWaitEvent(st2, c->pev[0], 0);
       for (int sl = 0; sl < S && e == hipSuccess; ++sl) {
         hipStream_t q = (sl & 1) ? st2 : st;
         const int z0 = sl * dz, z1 = z0 + dz;
-        e = run_slab_pass<T>(c, q, C_INV, psi, z0, z1, 0.0);
-        if (e == hipSuccess && sl == 0) {  // fork: st2 starts after the z-pass and slab 0's inverse y-pass
-          e = hipEventRecord(c->pev[0], st);
-          if (e == hipSuccess) e = hipStreamWaitEvent(st2, c->pev[0], 0);
-        }
-        if (e == hipSuccess) e = run_slab_pass<T>(c, q, X_MID, psi, z0, z1, d);
-        if (e == hipSuccess && fwd_next) e = run_slab_pass<T>(c, q, C_FWD, psi, z0, z1, 0.0);
+        e = run_slab_pass<T>(c, q, X_MID, psi, z0, z1, 0, d);
+        if (e == hipSuccess && y_next) e = run_slab_pass<T>(c, q, C_PROP, psi, z0, z1, tab[kn], lin[kn]);
       }
       if (e == hipSuccess) e = hipEventRecord(c->pev[1], st2);  // join
       if (e == hipSuccess) e = hipStreamWaitEvent(st, c->pev[1], 0);
@@ -565,20 +558,14 @@ int step_impl(sgp_ctx* c, void* psi, long nsteps) {
   return SGP_OK;
 }
 
-// Average duration of one pass launched reps times back to back on the context
-// stream, bracketed by HIP events.  pass: 0 X-pass (mid form), 1 linear pass along
-// y (2D: with the propagator; 3D: forward y), 2 z-pass with the propagator (3D),
-// 3 inverse y-pass (3D).
+// One launch of a pass for timing: 0 X-pass (mid form), 1 y-pass, 2 z-pass (3D).
 // ev: null, or an event pair that the dispatch stamps with the kernel's start and end.
 template <typename T>
 hipError_t launch_timed_pass(sgp_ctx* c, void* psi, int pass, bool first, const hipEvent_t* ev = nullptr) {
   // X-pass as inside a step: the clock from the device slots (set by the first launch)
   if (pass == 0)
     return run_xpass<T>(c, c->st, X_MID, psi, c->dprop[0], first ? CLOCK_ARG : CLOCK_DEVICE, c->t, ev);
-  if (pass == 1) return run_colpass<T>(c, c->st, c->g.dim == 2 ? C_PROP : (c->lin_split ? C_FSPIN : C_FWD), 1, psi, 0,
-                                       0.0, ev);
-  if (pass == 2) return run_colpass<T>(c, c->st, c->lin_split ? C_KIN : C_PROP, 2, psi, 0, 0.0, ev);
-  return run_colpass<T>(c, c->st, C_INV, 1, psi, 0, 0.0, ev);
+  return run_colpass<T>(c, c->st, pass == 1 ? C_PROP : C_KIN, pass, psi, 0, 0.0, ev);
 }
 
 // Events that a dispatch stamps for per-kernel timing: without the system-scope
@@ -588,12 +575,12 @@ hipError_t launch_timed_pass(sgp_ctx* c, void* psi, int pass, bool first, const 
 constexpr unsigned kTimingEventFlags = hipEventDisableSystemFence;
 
 // In-step timing: reps rounds of the passes of one linear + nonlinear substep in
-// step order (2D: y, X; 3D: y, z, inverse y, X); every launch of the timed pass
+// step order (2D: y, X; 3D: y, z, X); every launch of the timed pass
 // carries an event pair that its dispatch stamps with the kernel's start and end
 // (no marker packets between the kernels); the average of those durations.
 template <typename T>
 int time_pass_in_step(sgp_ctx* c, void* psi, int pass, int reps, double* avg_ms) {
-  const std::vector<int> order = c->g.dim == 2 ? std::vector<int>{1, 0} : std::vector<int>{1, 2, 3, 0};
+  const std::vector<int> order = c->g.dim == 2 ? std::vector<int>{1, 0} : std::vector<int>{1, 2, 0};
   std::vector<hipEvent_t> ev(2 * (size_t)reps, nullptr);
   hipError_t e = hipSuccess;
   for (size_t i = 0; i < ev.size() && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ev[i], kTimingEventFlags);
@@ -619,6 +606,8 @@ int time_pass_in_step(sgp_ctx* c, void* psi, int pass, int reps, double* avg_ms)
   return SGP_OK;
 }
 
+// Average duration of one pass launched reps times back to back on the context
+// stream, bracketed by HIP events.
 template <typename T>
 int time_pass_impl(sgp_ctx* c, void* psi, int pass, int reps, double* avg_ms) {
   if (pass & SGP_TIME_IN_STEP) return time_pass_in_step<T>(c, psi, pass & ~SGP_TIME_IN_STEP, reps, avg_ms);
@@ -1056,7 +1045,8 @@ int lab_step_impl(sgp_ctx* c, void* psi, long nsteps) {
 
 // Forward evolution of one call that also stores, for every pass with a pointwise
 // stage, the stage's input: slot 2k the input of the k-th nonlinear substep
-// (physical), slot 2k+1 the Fourier-space input of the k-th propagator.  Kernels are
+// (physical), slot 2k+1 the input of the k-th propagator in (nu_p, nu_q) (in 3D per
+// z-plane).  Kernels are
 // launched one by one (each pass writes a different slot).
 template <typename T>
 int step_store_impl(sgp_ctx* c, void* psi, long nsteps, char* store) {
@@ -1069,13 +1059,8 @@ int step_store_impl(sgp_ctx* c, void* psi, long nsteps, char* store) {
   double s = c->t;
   for (size_t k = 0; k < lin.size(); ++k) {
     char* sl = store + (2 * k + 1) * slot;
-    if (c->g.dim == 2) {
-      e = run_colpass_ex<T>(c, C_PROP, 1, psi, tab[k], lin[k], sl, nullptr);
-    } else {
-      e = run_colpass_ex<T>(c, C_FWD, 1, psi, tab[k], lin[k], nullptr, nullptr);
-      if (e == hipSuccess) e = run_colpass_ex<T>(c, C_PROP, 2, psi, tab[k], lin[k], sl, nullptr);
-      if (e == hipSuccess) e = run_colpass_ex<T>(c, C_INV, 1, psi, tab[k], lin[k], nullptr, nullptr);
-    }
+    e = run_colpass_ex<T>(c, C_PROP, 1, psi, tab[k], lin[k], sl, nullptr);
+    if (e == hipSuccess && c->g.dim == 3) e = run_colpass_ex<T>(c, C_KIN, 2, psi, tab[k], lin[k], nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "linear pass launch");
     s += lin[k];
     e = run_xpass_ex<T>(c, k + 1 == lin.size() ? X_LAST : X_MID, psi, nl[k + 1], CLOCK_ARG, s,
@@ -1103,14 +1088,9 @@ int adjoint_impl(sgp_ctx* c, void* lam, long nsteps, const char* store) {
   if (e != hipSuccess) return hip_fail(c, e, "adjoint X-pass launch");
   for (long k = (long)M - 1; k >= 0; --k) {
     const char* sl = store + (2 * k + 1) * slot;
-    if (c->g.dim == 2) {
-      e = run_colpass_ex<T>(c, C_ADJ, 1, lam, tab[k], lin[k], nullptr, sl);
-    } else {
-      // adjoint of (Y1 forward, Z, Y2 inverse): Y forward, Z adjoint, Y inverse
-      e = run_colpass_ex<T>(c, C_FWD, 1, lam, tab[k], lin[k], nullptr, nullptr);
-      if (e == hipSuccess) e = run_colpass_ex<T>(c, C_ADJ, 2, lam, tab[k], lin[k], nullptr, sl);
-      if (e == hipSuccess) e = run_colpass_ex<T>(c, C_INV, 1, lam, tab[k], lin[k], nullptr, nullptr);
-    }
+    // adjoint of (y-pass, z-pass): z-pass with the conjugate phase, then P^H along y
+    if (c->g.dim == 3) e = run_colpass_ex<T>(c, C_KIN, 2, lam, tab[k], lin[k], nullptr, nullptr, true);
+    if (e == hipSuccess) e = run_colpass_ex<T>(c, C_ADJ, 1, lam, tab[k], lin[k], nullptr, sl, true);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint linear pass launch");
     e = run_xpass_ex<T>(c, k == 0 ? XA_FIRST : XA_MID, lam, nl[k], CLOCK_ARG, s[k], nullptr, store + 2 * k * slot);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint X-pass launch");
@@ -1320,7 +1300,7 @@ int sgp_set_time(sgp_ctx* c, double t) {
 
 int sgp_time_pass(sgp_ctx* c, void* psi, int pass, int reps, double* avg_ms) {
   if (!c || !psi || !avg_ms || reps < 1) return fail(c, SGP_ERR_ARG, "bad argument");
-  const int kind = pass & 3;
+  int kind = pass & 3;
   if ((c->g.dim == 2 && kind > 1) || (pass & ~(SGP_TIME_IN_STEP | SGP_TIME_STEPS | 3)) ||
       ((pass & SGP_TIME_IN_STEP) && (pass & SGP_TIME_STEPS)))
     return fail(c, SGP_ERR_ARG, "no such pass");
@@ -1328,6 +1308,10 @@ int sgp_time_pass(sgp_ctx* c, void* psi, int pass, int reps, double* avg_ms) {
     return fail(c, SGP_ERR_ARG, "at most 4096 rounds or steps when every launch is timed");
   if (!c->ws) return fail(c, SGP_ERR_STATE, "no workspace set");
   if (!c->have_prop) return fail(c, SGP_ERR_STATE, "propagator not built");
+  if (kind == 3) {  // the inverse transform along y is part of the y-pass
+    kind = 1;
+    pass = (pass & ~3) | 1;
+  }
   if (pass & SGP_TIME_STEPS) {
     if (reps < 2) return fail(c, SGP_ERR_ARG, "SGP_TIME_STEPS needs at least 2 steps");
     if (c->frame == SGP_FRAME_LAB) return fail(c, SGP_ERR_STATE, "SGP_TIME_STEPS times the rotating-frame step");
@@ -1584,7 +1568,6 @@ hipError_t ens_upload_args(sgp_ensemble* e) {
         column_geometry(c, 1, a);
         a.cs = c->at(c->off_cs[S.table]);
         a.kin_a = c->at(c->off_kin[S.table][0]);
-        a.kin_o = c->at(c->off_kin[S.table][1]);
         a.kin_l = c->at(c->off_kin[S.table][1]);
         a.advance_clock = 1;
         a.n_line = c->g.n[1];
@@ -1788,7 +1771,6 @@ PassArgs ens_cargs(sgp_ctx* c, void* state, int kind, int table, double d, void*
   a.n_line = c->g.n[1];
   a.cs = c->at(c->off_cs[table]);
   a.kin_a = c->at(c->off_kin[table][0]);
-  a.kin_o = c->at(c->off_kin[table][1]);
   a.kin_l = c->at(c->off_kin[table][1]);
   a.d = d;
   a.advance_clock = kind == C_PROP ? 1 : 0;

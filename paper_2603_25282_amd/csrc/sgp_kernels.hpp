@@ -4,19 +4,18 @@
 
 namespace sgp {
 
-enum { X_FIRST = 0, X_MID = 1, X_LAST = 2, X_NLONLY = 3, C_PROP = 4, C_FWD = 5, C_INV = 6,
+enum { X_FIRST = 0, X_MID = 1, X_LAST = 2, X_NLONLY = 3,
+       // y-lines: FFT, exp(-i d (nu_x^2 + nu_y^2)/2) exp(i d Q) / N^d, inverse FFT
+       C_PROP = 4,
+       // z-lines (3D): FFT, exp(-i d nu_z^2/2), inverse FFT per component
+       C_KIN = 5,
        // adjoints: of X_FIRST (iFFT, NL adjoint), of X_MID (iFFT, NL adjoint, FFT),
        // of X_LAST (NL adjoint, FFT), of C_PROP (FFT, P^H and parameter partials, iFFT)
        XA_FIRST = 7, XA_MID = 8, XA_LAST = 9, C_ADJ = 10,
        // rotation mapping (RSDA shears, Sec. 3.1): FFT, phase exp(i nu a w), inverse FFT
        // along x (w = y of the line) or along y (w = x of the column); and bare
        // transforms along x (for the lab-frame Algorithm 1 mode)
-       X_SHEAR = 11, C_SHEAR = 12, X_FWD = 13, X_INV = 14,
-       // 3D linear substep with the propagator split by axis (its spin part depends on
-       // (nu_p, nu_q) only, Sec. 3.1's 3D remark, so it commutes with the z transform):
-       // y-lines FFT then exp(-i d (nu_x^2 + nu_y^2)/2) exp(i d Q) / N^3 (C_FSPIN), and
-       // z-lines FFT, exp(-i d nu_z^2/2), inverse FFT per component (C_KIN)
-       C_FSPIN = 15, C_KIN = 16 };
+       X_SHEAR = 11, C_SHEAR = 12, X_FWD = 13, X_INV = 14 };
 enum { NGRAD = 5 };  // adjoint parameter slots: gamma, Omega, c0, c1, c2
 // observables passes; OBS_JX / OBS_JY: the x-line and y-column parts of <u, J_z v>
 enum { OBS_X = 0, OBS_Y = 1, OBS_Z = 2, OBS_JX = 3, OBS_JY = 4 };
@@ -43,7 +42,6 @@ struct PassArgs {
   // propagator
   const void* cs;        // (C - 1, S) per (q, p)
   const void* kin_a;     // exp(-i d nu^2/2) - 1 along x
-  const void* kin_o;     // ... along the outer axis (3D z-lines: y)
   const void* kin_l;     // ... along the line
   double nu_scale_a;     // pi / Lx
   double nu_scale_q;     // pi / Ly
@@ -59,6 +57,7 @@ struct PassArgs {
   double s_arg;          // clock value passed by the host (CLOCK_ARG; then written to *clock)
   int clock_mode;
   int advance_clock;
+  int kin_conj;          // C_KIN: the conjugate phase (its adjoint)
   // batched passes
   void* state;           // the instance's state
   int n_line;            // length of the pass's lines

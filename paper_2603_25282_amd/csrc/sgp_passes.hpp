@@ -10,8 +10,15 @@
 //                           wavevector (eq. sl1), inverse FFT along y.
 // Between passes the state is held x-transformed (Fourier in x, physical in y).
 // The first X-pass of a call starts from physical data (no inverse FFT) and the
-// last one ends in physical data (no forward FFT).  3D: Y1 (forward y),
-// Z (forward z, propagator, inverse z), Y2 (inverse y).
+// last one ends in physical data (no forward FFT).
+// 3D adds one pass: the propagator is the product of its part in (nu_p, nu_q) (spin and
+// in-plane kinetic) and exp(-i d nu_r^2/2) (Sec. 3.1, 3D: Q does not depend on nu_r), and
+// the first acts on each z-plane, the second on each z-line alone.  So the Y-pass applies
+// the former and goes back to y at once, and the
+//   Z-pass (lines along z): forward FFT along z, z kinetic phase, inverse FFT along z
+// needs no transform along y around it: three round trips of the state per substep.
+// (Four round trips, with the y transforms in passes of their own around a z-pass,
+// measured 0.479 against 0.419 ms per TS4 step at 128^3 and 4.60 against 3.86 at 256^3.)
 //
 // Work split inside a block: W lines x 5 components; each (line, component) is
 // transformed by TL = N/E threads holding E elements each (register Stockham FFT
@@ -60,7 +67,7 @@ __device__ __forceinline__ void trap_angle(const PassArgs& a, double& c, double&
 // Generic pass.  KIND selects the line direction and the stages:
 //   X_FIRST: load phys -> NL -> FFTx -> store       X_MID: iFFTx -> NL -> FFTx
 //   X_LAST:  iFFTx -> NL -> store phys              X_NLONLY: NL only
-//   C_PROP:  FFT -> propagator -> iFFT (column)     C_FWD / C_INV: FFT / iFFT only
+//   C_PROP:  FFT -> propagator -> iFFT (y column)   C_KIN: FFT -> phase -> iFFT (z column)
 // ---------------------------------------------------------------------------
 template <int KIND> struct KindInfo {
   static constexpr bool XL = KIND == X_FIRST || KIND == X_MID || KIND == X_LAST || KIND == X_NLONLY ||
@@ -70,14 +77,12 @@ template <int KIND> struct KindInfo {
   static constexpr bool XADJ = KIND == XA_FIRST || KIND == XA_MID || KIND == XA_LAST;
   static constexpr bool ADJ = XADJ || KIND == C_ADJ;
   static constexpr bool PW = (XL && !SHEAR && KIND != X_FWD && KIND != X_INV) || KIND == C_PROP ||
-                             KIND == C_ADJ || KIND == C_FSPIN;  // has a pointwise stage (on the LDS tile)
+                             KIND == C_ADJ;  // has a pointwise stage (on the LDS tile)
   // which transforms the pass runs (forward: exp(-i..), inverse: exp(+i..))
   static constexpr bool HF = KIND == X_FIRST || KIND == X_MID || KIND == XA_MID || KIND == XA_LAST ||
-                             KIND == C_PROP || KIND == C_FWD || KIND == C_ADJ || SHEAR || KIND == X_FWD ||
-                             KIND == C_FSPIN || KIND == C_KIN;
+                             KIND == C_PROP || KIND == C_ADJ || SHEAR || KIND == X_FWD || KIND == C_KIN;
   static constexpr bool HI = KIND == X_MID || KIND == X_LAST || KIND == XA_FIRST || KIND == XA_MID ||
-                             KIND == C_PROP || KIND == C_INV || KIND == C_ADJ || SHEAR || KIND == X_INV ||
-                             KIND == C_KIN;
+                             KIND == C_PROP || KIND == C_ADJ || SHEAR || KIND == X_INV || KIND == C_KIN;
 };
 
 // LDS cx<T> values of the staged twiddle tables of a pass (forward table first).
@@ -151,19 +156,21 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   if constexpr (TWF > 0) stage_tw<T, NT, TWF>(ltw, a.tw_fwd, tid);
   if constexpr (TWI > 0) stage_tw<T, NT, TWI>(ltw + TWF, a.tw_inv, tid);
 
-  if constexpr (KIND == X_MID || KIND == X_LAST || KIND == C_INV || KIND == XA_FIRST || KIND == XA_MID ||
-                KIND == X_INV)
+  if constexpr (KIND == X_MID || KIND == X_LAST || KIND == XA_FIRST || KIND == XA_MID || KIND == X_INV)
     fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
-  if constexpr (KIND == C_PROP || KIND == C_FWD || KIND == C_ADJ || KIND == X_FWD || KindInfo<KIND>::SHEAR ||
-                KIND == C_FSPIN || KIND == C_KIN)
+  if constexpr (KIND == C_PROP || KIND == C_ADJ || KIND == X_FWD || KindInfo<KIND>::SHEAR || KIND == C_KIN)
     fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, twf, 0);
 
   if constexpr (KIND == C_KIN) {
     // the kinetic phase along the line, per component: coefficient k times
     // exp(-i d nu_k^2/2), in increment form (table entry exp(..) - 1)
     const cx<T>* kin_l = reinterpret_cast<const cx<T>*>(a.kin_l);
+    const T sg = a.kin_conj ? T(-1) : T(1);
 #pragma unroll
-    for (int m = 0; m < E; ++m) v[0][m] = inc_apply(kin_l[t + TL * m], v[0][m]);
+    for (int m = 0; m < E; ++m) {
+      const cx<T> ph = kin_l[t + TL * m];
+      v[0][m] = inc_apply(mk<T>(ph.re, sg * ph.im), v[0][m]);
+    }
     fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
   }
 
@@ -266,74 +273,20 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
     } else {
       const T* cs = reinterpret_cast<const T*>(a.cs);
       const cx<T>* kin_a = reinterpret_cast<const cx<T>*>(a.kin_a);
-      const cx<T>* kin_o = reinterpret_cast<const cx<T>*>(a.kin_o);
       const cx<T>* kin_l = reinterpret_cast<const cx<T>*>(a.kin_l);
       const T Om = T(a.Omega), ga = T(a.gamma), norm = T(a.norm);
       // 1/N^d as a (hi, lo) pair: exact for powers of two, compensated otherwise
       const T norm_lo = T(a.norm - (double)norm);
       const int nxx = (int)a.ncols;
-      if constexpr (KIND == C_PROP) {
-        if (a.dim == 3) {
-          // z-lines: the spin part of the propagator and the kinetic phase along x and
-          // y belong to the column (kx, ky), the same for every kz of it; each is
-          // prepared once per column and shared through LDS
-          __shared__ Sym4Prep<T> cprep[W];
-          __shared__ cx<T> ckin[W];
-          if (tid < W) {
-            const int kx = kx0 + tid < nxx ? kx0 + tid : 0;
-            const int px = kx < nxx / 2 ? kx : kx - nxx;
-            const int pq = (int)o < a.n_q / 2 ? (int)o : (int)o - a.n_q;
-            const int qidx = kx * a.n_q + (int)o;
-            const T Cm1 = cs[2 * qidx], S = cs[2 * qidx + 1];
-            const cx<T> as = mk<T>(Cm1, -S * Om);
-            const cx<T> beta = mk<T>(S * ga * T(px * a.nu_scale_a), -S * ga * T(pq * a.nu_scale_q));
-            cprep[tid] = sym4_prepare<T>(as, beta);
-            const cx<T> ka = kin_a[kx], ko = kin_o[o];
-            ckin[tid] = ka + ko + ka * ko;
-          }
-          __syncthreads();
-          for (int pt = tid; pt < W * N; pt += NT) {
-            const int pc = pt / N, kl = pt % N;
-            const cx<T> ka = ckin[pc], kl1 = kin_l[kl];
-            const cx<T> ss = ka + kl1 + ka * kl1;  // kinetic phase - 1
-            cx<T> p[5];
-            if (norm_lo == T(0)) {
-#pragma unroll
-              for (int cc = 0; cc < 5; ++cc) p[cc] = norm * lx[pt * 5 + cc];
-            } else {
-#pragma unroll
-              for (int cc = 0; cc < 5; ++cc)
-                p[cc] = mk<T>(kmul<T>(norm, norm_lo, lx[pt * 5 + cc].re), kmul<T>(norm, norm_lo, lx[pt * 5 + cc].im));
-            }
-            sym4_apply_prep<T>(cprep[pc], ss, p);
-#pragma unroll
-            for (int cc = 0; cc < 5; ++cc) lx[pt * 5 + cc] = p[cc];
-          }
-        }
-      }
       for (int pt = tid; pt < W * N; pt += NT) {
-        if constexpr (KIND == C_PROP) {
-          if (a.dim == 3) break;  // done above
-        }
         const int pc = pt / N, kl = pt % N;
         const int kx = kx0 + pc < nxx ? kx0 + pc : 0;
         const int px = kx < nxx / 2 ? kx : kx - nxx;
         const T nup = T(px * a.nu_scale_a);
-        int kq;
-        int qidx;
-        cx<T> ka = kin_a[kx];
-        // table kx-major: a column block reads its entries contiguously (2D, and the
-        // 3D y-lines of C_FSPIN) or one broadcast entry (3D z-lines)
-        if (a.dim == 2 || KIND == C_FSPIN) {
-          kq = kl;
-          qidx = kx * a.n_q + kl;
-        } else {
-          kq = (int)o;
-          qidx = kx * a.n_q + o;
-          const cx<T> ko = kin_o[o];
-          ka = ka + ko + ka * ko;
-        }
-        const int pq = kq < a.n_q / 2 ? kq : kq - a.n_q;
+        const cx<T> ka = kin_a[kx];
+        // table kx-major: a column block reads its entries contiguously
+        const int qidx = kx * a.n_q + kl;
+        const int pq = kl < a.n_q / 2 ? kl : kl - a.n_q;
         const T nuq = T(pq * a.nu_scale_q);
         const T Cm1 = cs[2 * qidx], S = cs[2 * qidx + 1];
         // alpha - 1 = (C - 1) - i S Omega; beta = i S gamma a = S gamma (nu_p - i nu_q)
@@ -440,7 +393,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       a.clock[2] = sn;
     }
   }
-  if constexpr (KIND == C_PROP || KIND == C_FSPIN) {
+  if constexpr (KIND == C_PROP || KIND == C_KIN) {
     if (a.advance_clock && tile == 0 && tid == 0) {
       const double s1 = a.clock[0] + a.d;
       double sn, cn;
@@ -598,8 +551,7 @@ static hipError_t pass_kind(int kind, cx<T>* psi, const PassArgs& a, hipStream_t
     case X_LAST: return pass_n<T, N, E, X_LAST>(psi, a, st, ev);
     case X_NLONLY: return pass_n<T, N, E, X_NLONLY>(psi, a, st, ev);
     case C_PROP: return pass_n<T, N, E, C_PROP>(psi, a, st, ev);
-    case C_FWD: return pass_n<T, N, E, C_FWD>(psi, a, st, ev);
-    case C_INV: return pass_n<T, N, E, C_INV>(psi, a, st, ev);
+    case C_KIN: return pass_n<T, N, E, C_KIN>(psi, a, st, ev);
     case XA_FIRST: return pass_n<T, N, E, XA_FIRST>(psi, a, st, ev);
     case XA_MID: return pass_n<T, N, E, XA_MID>(psi, a, st, ev);
     case XA_LAST: return pass_n<T, N, E, XA_LAST>(psi, a, st, ev);
@@ -608,8 +560,6 @@ static hipError_t pass_kind(int kind, cx<T>* psi, const PassArgs& a, hipStream_t
     case C_SHEAR: return pass_n<T, N, E, C_SHEAR>(psi, a, st, ev);
     case X_FWD: return pass_n<T, N, E, X_FWD>(psi, a, st, ev);
     case X_INV: return pass_n<T, N, E, X_INV>(psi, a, st, ev);
-    case C_FSPIN: return pass_n<T, N, E, C_FSPIN>(psi, a, st, ev);
-    case C_KIN: return pass_n<T, N, E, C_KIN>(psi, a, st, ev);
     default: return hipErrorInvalidValue;
   }
 }

@@ -271,8 +271,8 @@ class Solver:
 
     def get_plan(self):
         """Plan width E of the passes along x, y (, z); in 3D a fourth entry, the
-        linear substep's split (SGP_PLAN_LINEAR: 0 = the whole propagator in the
-        z-pass, 1 = its spin part in the forward y-pass)."""
+        linear substep's split (SGP_PLAN_LINEAR: 0 = the in-plane part in the y-pass,
+        then the z kinetic phase in the z-pass; 1 = the z-pass first)."""
         e = ctypes.c_int()
         out = []
         for ax in range(len(self.shape)) if len(self.shape) == 2 else (0, 1, 2, SGP_PLAN_LINEAR):
