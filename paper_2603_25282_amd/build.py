@@ -14,6 +14,10 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # no packed FP32 instructions (v_pk_*_f32) anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # multiply-adds are fused within an expression only: which ones are is then a property
+    # of the source and not of the kernel they are inlined into, so that every kernel that
+    # runs a line (alone, in an ensemble, any block shape) gives the same bits
+    "-ffp-contract=on",
     "-Wno-unused-command-line-argument",
 ]
 

@@ -228,6 +228,13 @@ PassArgs base_args(const sgp_ctx* c) {
   return a;
 }
 
+// Host clock of an x-pass (CLOCK_ARG): the trap's rotation angle Omega s.
+void host_clock(PassArgs& a, double s) {
+  a.s_arg = s;
+  a.trap_c = std::cos(a.Omega * s);
+  a.trap_s = std::sin(a.Omega * s);
+}
+
 // Column geometry for lines along `axis` (1 = y, 2 = z).
 void column_geometry(const sgp_ctx* c, int axis, PassArgs& a) {
   const int nx = c->g.n[0], ny = c->g.n[1], nz = c->g.dim == 3 ? c->g.n[2] : 1;
@@ -263,7 +270,7 @@ hipError_t run_xpass(sgp_ctx* c, hipStream_t st, int mode, void* psi, double d, 
   a.tw_fwd = c->at(c->off_tw[0][0]);
   a.tw_inv = c->at(c->off_tw[0][1]);
   a.d = d;
-  a.s_arg = s_arg;
+  host_clock(a, s_arg);
   a.clock_mode = clock_mode;
   if (!ev) ev = timing_events(c, mode == X_MID ? 0 : -1);
   return launch_pass<T>(mode, psi, a, c->g.n[0], c->elems(0), st, ev);
@@ -289,7 +296,7 @@ hipError_t run_xpass_ex(sgp_ctx* c, int kind, void* psi, double d, int clock_mod
   a.tw_fwd = c->at(c->off_tw[0][0]);
   a.tw_inv = c->at(c->off_tw[0][1]);
   a.d = d;
-  a.s_arg = s_arg;
+  host_clock(a, s_arg);
   a.clock_mode = clock_mode;
   a.store = store;
   a.fwd = fwd;
@@ -1056,14 +1063,13 @@ int step_store_impl(sgp_ctx* c, void* psi, long nsteps, char* store) {
   const size_t slot = (size_t)c->npts() * 5 * 2 * c->esize;
   hipError_t e = run_xpass_ex<T>(c, X_FIRST, psi, nl[0], CLOCK_ARG, c->t, store, nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "X-pass launch");
-  double s = c->t;
   for (size_t k = 0; k < lin.size(); ++k) {
     char* sl = store + (2 * k + 1) * slot;
     e = run_colpass_ex<T>(c, C_PROP, 1, psi, tab[k], lin[k], sl, nullptr);
     if (e == hipSuccess && c->g.dim == 3) e = run_colpass_ex<T>(c, C_KIN, 2, psi, tab[k], lin[k], nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "linear pass launch");
-    s += lin[k];
-    e = run_xpass_ex<T>(c, k + 1 == lin.size() ? X_LAST : X_MID, psi, nl[k + 1], CLOCK_ARG, s,
+    // the device clock, as in sgp_step: the same trap angles to the last bit
+    e = run_xpass_ex<T>(c, k + 1 == lin.size() ? X_LAST : X_MID, psi, nl[k + 1], CLOCK_DEVICE, 0.0,
                         store + (2 * k + 2) * slot, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "X-pass launch");
   }
@@ -1562,7 +1568,7 @@ hipError_t ens_upload_args(sgp_ensemble* e) {
         a.tw_fwd = c->at(c->off_tw[0][0]);
         a.tw_inv = c->at(c->off_tw[0][1]);
         a.clock_mode = S.kind == X_FIRST ? CLOCK_ARG : CLOCK_DEVICE;
-        a.s_arg = e->t;
+        host_clock(a, e->t);
         a.n_line = c->g.n[0];
       } else {
         column_geometry(c, 1, a);
@@ -1748,6 +1754,8 @@ size_t ens_inst_store(const sgp_ensemble* e, int i, long nsteps) {
   return align256(b);
 }
 
+// Forward passes after the first read the device clock, as ens_step does; the adjoint's
+// take the host's value.
 PassArgs ens_xargs(sgp_ctx* c, void* state, int kind, double d, double s, void* store, const void* fwd) {
   PassArgs a = base_args(c);
   a.state = state;
@@ -1755,12 +1763,11 @@ PassArgs ens_xargs(sgp_ctx* c, void* state, int kind, double d, double s, void* 
   a.tw_fwd = c->at(c->off_tw[0][0]);
   a.tw_inv = c->at(c->off_tw[0][1]);
   a.d = d;
-  a.s_arg = s;
-  a.clock_mode = CLOCK_ARG;
+  host_clock(a, s);
+  a.clock_mode = kind == X_MID || kind == X_LAST ? CLOCK_DEVICE : CLOCK_ARG;
   a.store = store;
   a.fwd = fwd;
   a.gacc = (double*)c->at(c->off_gacc);
-  (void)kind;
   return a;
 }
 

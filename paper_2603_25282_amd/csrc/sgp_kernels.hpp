@@ -55,6 +55,7 @@ struct PassArgs {
   double d;              // substep duration (nonlinear: the flow time; linear: the clock advance)
   double* clock;         // device clock s of the rotating frame
   double s_arg;          // clock value passed by the host (CLOCK_ARG; then written to *clock)
+  double trap_c, trap_s; // cos and sin of Omega s_arg (CLOCK_ARG)
   int clock_mode;
   int advance_clock;
   int kin_conj;          // C_KIN: the conjugate phase (its adjoint)

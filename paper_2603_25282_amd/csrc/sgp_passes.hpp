@@ -51,16 +51,23 @@ __device__ __forceinline__ long xcd_tile(long b, long nblocks) {
   return (b % 8) * (nblocks / 8) + b / 8;
 }
 
-// Trap rotation cos/sin(Omega s): from the host value (first pass of a call) or from
-// the device clock, whose slots 1, 2 hold cos and sin of the current angle (written by
-// whichever pass last moved the clock).
+// Trap rotation cos/sin(Omega s): the host's values (first pass of a call, adjoint passes)
+// or the device clock's slots 1, 2, which hold cos and sin of the current angle (written
+// by whichever pass last moved the clock).
 __device__ __forceinline__ void trap_angle(const PassArgs& a, double& c, double& s) {
-  if (a.clock_mode == CLOCK_ARG) {
-    sincos(a.Omega * a.s_arg, &s, &c);
-  } else {
-    c = a.clock[1];
-    s = a.clock[2];
-  }
+  const double* src = a.clock_mode == CLOCK_ARG ? nullptr : a.clock;
+  c = src ? src[1] : a.trap_c;
+  s = src ? src[2] : a.trap_s;
+}
+
+// Move the device clock by a.d (one thread).
+__device__ __forceinline__ void advance_clock(const PassArgs& a) {
+  const double s1 = a.clock[0] + a.d;
+  double sn, cn;
+  sincos(a.Omega * s1, &sn, &cn);
+  a.clock[0] = s1;
+  a.clock[1] = cn;
+  a.clock[2] = sn;
 }
 
 // ---------------------------------------------------------------------------
@@ -125,11 +132,15 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   int estride;      // element stride between consecutive points of the line
   int line0 = 0;    // x-lines: first line of the block (line = z * ny + y)
   int o = 0, kx0 = 0;
+  // one line per block: no idle lines, and the loads need no guard (with more lines per
+  // block the guards keep the compiler from holding all addresses at once: without them
+  // the 256^3 x-pass took 571 instead of 465 us)
+  constexpr bool FULL = W == 1;
   bool active;
   if constexpr (XL) {
     line0 = (int)tile * W;
     const int line = line0 + col;
-    active = line < a.nlines;
+    active = FULL || line < a.nlines;
     base = (active ? line : 0) * N * 5;
     estride = 5;
   } else {
@@ -137,7 +148,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
     o = (int)tile / ncolblk;
     kx0 = ((int)tile % ncolblk) * W;
     const int kx = kx0 + col;
-    active = kx < a.ncols;
+    active = FULL || kx < a.ncols;
     base = o * (int)a.outer_stride + (active ? kx : 0) * 5;
     estride = (int)a.stride;
   }
@@ -155,6 +166,34 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   const cx<T>* twi = ltw + TWF;
   if constexpr (TWF > 0) stage_tw<T, NT, TWF>(ltw, a.tw_fwd, tid);
   if constexpr (TWI > 0) stage_tw<T, NT, TWI>(ltw + TWF, a.tw_inv, tid);
+
+  // read here, with the state loads: at its place of use, behind the transform and its
+  // barriers, the clock is a round trip to memory of its own in every block
+  double ct = 1.0, st = 0.0;
+  if constexpr (XL && PW) trap_angle(a, ct, st);
+
+  // propagator tables of this thread's points.  With one line per block (few blocks, all
+  // of them in the same phase) they are loaded here, under the state loads; with more
+  // lines per block other wavefronts cover the loads at their place of use, and the
+  // registers are worth more.
+  constexpr int PP = (W * N + NT - 1) / NT;  // points per thread
+  constexpr bool PRE = !XL && PW && W == 1;
+  [[maybe_unused]] constexpr int UN = PRE ? PP : 1;
+  T pcs[PRE ? PP : 1][2];
+  cx<T> pkl[PRE ? PP : 1];
+  cx<T> pka = mk<T>(T(0), T(0));
+  if constexpr (PRE) {
+    const T* cs = reinterpret_cast<const T*>(a.cs) + 2 * (size_t)(kx0 * a.n_q);
+    const cx<T>* kl = reinterpret_cast<const cx<T>*>(a.kin_l);
+    pka = reinterpret_cast<const cx<T>*>(a.kin_a)[kx0];
+#pragma unroll
+    for (int i = 0; i < PP; ++i) {
+      const int pt = tid + i * NT < N ? tid + i * NT : 0;
+      pcs[i][0] = cs[2 * pt];
+      pcs[i][1] = cs[2 * pt + 1];
+      pkl[i] = kl[pt];
+    }
+  }
 
   if constexpr (KIND == X_MID || KIND == X_LAST || KIND == XA_FIRST || KIND == XA_MID || KIND == X_INV)
     fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
@@ -225,8 +264,6 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       K.c0p = a.c0p;
       K.c1 = a.c1;
       K.c2 = a.c2;
-      double ct, st;
-      trap_angle(a, ct, st);
       // (y, z) indices of the block's first line (uniform); the block's W lines follow it
       // (z from the launch's first plane a.z0 on)
       const int izl = a.dim == 3 ? line0 / a.ny : 0;
@@ -278,21 +315,34 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       // 1/N^d as a (hi, lo) pair: exact for powers of two, compensated otherwise
       const T norm_lo = T(a.norm - (double)norm);
       const int nxx = (int)a.ncols;
-      for (int pt = tid; pt < W * N; pt += NT) {
+#pragma unroll UN
+      for (int i = 0; i < PP; ++i) {
+        const int pt = tid + i * NT;
+        if (pt >= W * N) break;
         const int pc = pt / N, kl = pt % N;
         const int kx = kx0 + pc < nxx ? kx0 + pc : 0;
         const int px = kx < nxx / 2 ? kx : kx - nxx;
         const T nup = T(px * a.nu_scale_a);
-        const cx<T> ka = kin_a[kx];
         // table kx-major: a column block reads its entries contiguously
-        const int qidx = kx * a.n_q + kl;
+        cx<T> ka, kl1;
+        T Cm1, S;
+        if constexpr (PRE) {
+          ka = pka;
+          kl1 = pkl[i];
+          Cm1 = pcs[i][0];
+          S = pcs[i][1];
+        } else {
+          const int qidx = kx * a.n_q + kl;
+          ka = kin_a[kx];
+          kl1 = kin_l[kl];
+          Cm1 = cs[2 * qidx];
+          S = cs[2 * qidx + 1];
+        }
         const int pq = kl < a.n_q / 2 ? kl : kl - a.n_q;
         const T nuq = T(pq * a.nu_scale_q);
-        const T Cm1 = cs[2 * qidx], S = cs[2 * qidx + 1];
         // alpha - 1 = (C - 1) - i S Omega; beta = i S gamma a = S gamma (nu_p - i nu_q)
         const cx<T> as = mk<T>(Cm1, -S * Om);
         const cx<T> beta = mk<T>(S * ga * nup, -S * ga * nuq);
-        const cx<T> kl1 = kin_l[kl];
         const cx<T> ss = ka + kl1 + ka * kl1;  // kinetic phase - 1
         cx<T> p[5];
         if (norm_lo == T(0)) {
@@ -387,24 +437,15 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   if constexpr (XL && !ADJ && PW) {
     if (a.clock_mode == CLOCK_ARG && tile == 0 && tid == 0) {
       a.clock[0] = a.s_arg;
-      double sn, cn;
-      sincos(a.Omega * a.s_arg, &sn, &cn);
-      a.clock[1] = cn;
-      a.clock[2] = sn;
-    }
-  }
-  if constexpr (KIND == C_PROP || KIND == C_KIN) {
-    if (a.advance_clock && tile == 0 && tid == 0) {
-      const double s1 = a.clock[0] + a.d;
-      double sn, cn;
-      sincos(a.Omega * s1, &sn, &cn);
-      a.clock[0] = s1;
-      a.clock[1] = cn;
-      a.clock[2] = sn;
+      a.clock[1] = ct;
+      a.clock[2] = st;
     }
   }
 }
 
+// The device clock's advance runs in a block of its own, after the tiles' blocks (see
+// pass_blocks): in a tile's block its load and sine ended every pass of a small grid
+// ~2 us after the other blocks.
 template <typename T, int N, int E, int W, int KIND>
 __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ psi, PassArgs a) {
   constexpr int BUF = pass_lds<N, W, KIND>();
@@ -413,8 +454,17 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ ps
   __shared__ cx<T> lx[BUF];
   __shared__ uint4 ltw[TWB > 0 ? TWB : 1];
   __shared__ double gred[KindInfo<KIND>::ADJ ? NT / 64 + 1 : 1][NGRAD];
-  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, gridDim.x), lx, reinterpret_cast<cx<T>*>(ltw),
-                              gred);
+  long nb = gridDim.x;
+  if constexpr (KIND == C_PROP || KIND == C_KIN) {
+    if (a.advance_clock) {
+      nb -= 1;
+      if (blockIdx.x == nb) {
+        if (threadIdx.x == 0) advance_clock(a);
+        return;
+      }
+    }
+  }
+  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, nb), lx, reinterpret_cast<cx<T>*>(ltw), gred);
 }
 
 // ---------------------------------------------------------------------------
@@ -457,11 +507,14 @@ __global__ __launch_bounds__(320) void k_pass_batched(const int2* __restrict__ i
   __shared__ double gred[KindInfo<KIND>::ADJ ? 6 : 1][NGRAD];
   const int2 it = items[blockIdx.x];
   const PassArgs& a = args[it.x];
+  if constexpr (KIND == C_PROP) {
+    if (a.advance_clock && it.y == 0 && threadIdx.x == 319) advance_clock(a);
+  }
   cx<T>* psi = reinterpret_cast<cx<T>*>(a.state);
 #define SGP_BCASE(NN)                                                                                  \
   case NN:                                                                                             \
     if constexpr (NN <= NMAX && batched_plan_ok(NN, E, ES))                                            \
-      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw, gred);                   \
+      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw, gred);                  \
     break;
   switch (a.n_line) {
     SGP_BCASE(64) SGP_BCASE(128) SGP_BCASE(192) SGP_BCASE(256) SGP_BCASE(384) SGP_BCASE(512) SGP_BCASE(768)
@@ -528,19 +581,36 @@ struct Geo {
   static constexpr int NT = W * 5 * TL;
 };
 
+// Blocks of a pass with W lines per block.
+template <int W, int KIND>
+static long pass_blocks(const PassArgs& a) {
+  return KindInfo<KIND>::XL ? (a.nlines + W - 1) / W : ((a.ncols + W - 1) / W) * a.nouter;
+}
+
 // ev: null, or two events that the dispatch itself stamps with the kernel's start
 // and end (timing without marker packets between the kernels).
+template <typename T, int N, int E, int W, int KIND>
+static hipError_t pass_w(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
+  constexpr int NT = W * 5 * (N / E);
+  const long nblocks = pass_blocks<W, KIND>(a) + ((KIND == C_PROP || KIND == C_KIN) && a.advance_clock ? 1 : 0);
+  if (ev)
+    hipExtLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(NT), 0, st, ev[0], ev[1], 0, psi,
+                          a);
+  else
+    hipLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(NT), 0, st, psi, a);
+  return hipGetLastError();
+}
+
+// Lines per block: Geo's W, or one line where that would leave CUs without a block
+// (fewer than 256 blocks).  The arithmetic of a line does not depend on W; the adjoint
+// passes keep Geo's W, which fixes the grouping of their parameter partials.
 template <typename T, int N, int E, int KIND>
 static hipError_t pass_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
   constexpr int W = Geo<N, E>::W;
-  constexpr bool XL = KindInfo<KIND>::XL;
-  long nblocks = XL ? (a.nlines + W - 1) / W : ((a.ncols + W - 1) / W) * a.nouter;
-  if (ev)
-    hipExtLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(Geo<N, E>::NT), 0, st, ev[0],
-                          ev[1], 0, psi, a);
-  else
-    hipLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(Geo<N, E>::NT), 0, st, psi, a);
-  return hipGetLastError();
+  if constexpr (W > 1 && !KindInfo<KIND>::ADJ) {
+    if (pass_blocks<W, KIND>(a) < 256) return pass_w<T, N, E, 1, KIND>(psi, a, st, ev);
+  }
+  return pass_w<T, N, E, W, KIND>(psi, a, st, ev);
 }
 
 template <typename T, int N, int E>
