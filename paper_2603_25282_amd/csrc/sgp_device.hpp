@@ -38,6 +38,14 @@ template <typename T> __device__ __forceinline__ cx<T> cfma(cx<T> a, cx<T> b, cx
   return mk<T>(acc.re + a.re * b.re - a.im * b.im, acc.im + a.re * b.im + a.im * b.re);
 }
 
+// acc - a * b, and acc + conj(a) * b
+template <typename T> __device__ __forceinline__ cx<T> cfnma(cx<T> a, cx<T> b, cx<T> acc) {
+  return mk<T>(acc.re - a.re * b.re + a.im * b.im, acc.im - a.re * b.im - a.im * b.re);
+}
+template <typename T> __device__ __forceinline__ cx<T> cfmac(cx<T> a, cx<T> b, cx<T> acc) {
+  return mk<T>(acc.re + a.re * b.re + a.im * b.im, acc.im + a.re * b.im - a.im * b.re);
+}
+
 // x + a x for a factor 1 + a close to 1, with the product a x formed before the sum.
 // In cfma's order the small real part of a (of second order in the angle, for a
 // unit-modulus factor) is added to x alone and rounds away whenever it is below half
@@ -493,7 +501,7 @@ __device__ __forceinline__ void fft_line(cx<T> (&v)[NC][E], cx<T>* lx, int t, co
 
 // ---------------------------------------------------------------------------
 // Spin-2 rotation as the 4th symmetric power of U = [[alpha, beta], [-conj(beta),
-// conj(alpha)]] (|alpha|^2 + |beta|^2 = 1), times a scalar `scale`, applied to x.
+// conj(alpha)]] (|alpha|^2 + |beta|^2 = 1), applied to x.
 //
 // A 5-vector x (order m = 2..-2) is the binary quartic form sum_k x_k sqrt(C(4,k))
 // u^k v^(4-k), k = m + 2; U acts by u -> U11 u + U21 v, v -> U12 u + U22 v.
@@ -506,15 +514,14 @@ __device__ __forceinline__ void fft_line(cx<T> (&v)[NC][E], cx<T>* lx, int t, co
 // spin-2 matrices f of Sec. 1 under this representation, so
 // exp(i t n.sigma/2) -> exp(i t n.f).
 //
-// Inputs come in increment form: alpha = 1 + as, scale = 1 + ss.  Every update is
+// alpha comes in increment form, alpha = 1 + as.  Every update is
 // x <- x + (small coefficient) * x, so a coefficient's rounding error scales with
 // the coefficient and the near-identity maps of small time steps repeat no O(1)
 // rounding error from step to step.
 // ---------------------------------------------------------------------------
-// The factorisation of U (or of U P) depends on alpha and beta only; the scalar
-// factor enters only the diagonal.  sym4_prepare computes the factorisation once
-// (for many vectors rotated by the same U, e.g. every kz of one (kx, ky) column),
-// sym4_apply_prep applies it with a scale 1 + ss.
+// A scalar factor (phase, normalisation) is applied by the caller where it costs least:
+// folded into the nonlinear flow's coefficients (nl_point) or with the normalisation
+// (scale_phase); as a factor of the diagonal it took 24 more operations per point.
 template <typename T>
 struct Sym4Prep {
   cx<T> r, l;   // Taylor-shift coefficients of R and L
@@ -562,7 +569,7 @@ __device__ __forceinline__ Sym4Prep<T> sym4_prepare(cx<T> as, cx<T> beta) {
 }
 
 template <typename T>
-__device__ __forceinline__ void sym4_apply_prep(const Sym4Prep<T>& P, cx<T> ss, cx<T> (&x)[5]) {
+__device__ __forceinline__ void sym4_apply_prep(const Sym4Prep<T>& P, cx<T> (&x)[5]) {
   const T rho0 = T(2), rho1 = T(1.22474487139158904909864203735294570), rho2 = T(0.81649658092772603273242802490196380),
           rho3 = T(0.5);
   if (P.pivot) {
@@ -586,15 +593,11 @@ __device__ __forceinline__ void sym4_apply_prep(const Sym4Prep<T>& P, cx<T> ss, 
   x[3] = cfma(rr3, x[4], x[3]);
   x[2] = cfma(rr2, x[3], x[2]);
   x[3] = cfma(rr3, x[4], x[3]);
-  // D: x_j += eps_j x_j with 1 + eps_j = (1 + m_j)(1 + ss) (m at k = 2 is 0)
-  cx<T> eps[5];
-  eps[0] = P.m[0] + ss + P.m[0] * ss;
-  eps[1] = P.m[1] + ss + P.m[1] * ss;
-  eps[2] = ss;
-  eps[3] = P.m[2] + ss + P.m[2] * ss;
-  eps[4] = P.m[3] + ss + P.m[3] * ss;
-#pragma unroll
-  for (int j = 0; j < 5; ++j) x[j] = inc_apply(eps[j], x[j]);
+  // D: x_j += m_j x_j (m at k = 2 is 0)
+  x[0] = inc_apply(P.m[0], x[0]);
+  x[1] = inc_apply(P.m[1], x[1]);
+  x[3] = inc_apply(P.m[2], x[3]);
+  x[4] = inc_apply(P.m[3], x[4]);
   // L: Taylor shift on the reversed vector, x_(4-k) += l rho_k x_(3-k)
   x[1] = cfma(lr3, x[0], x[1]);
   x[2] = cfma(lr2, x[1], x[2]);
@@ -609,8 +612,20 @@ __device__ __forceinline__ void sym4_apply_prep(const Sym4Prep<T>& P, cx<T> ss, 
 }
 
 template <typename T>
-__device__ __forceinline__ void sym4_apply_inc(cx<T> as, cx<T> beta, cx<T> ss, cx<T> (&x)[5]) {
-  sym4_apply_prep<T>(sym4_prepare<T>(as, beta), ss, x);
+__device__ __forceinline__ void sym4_apply_inc(cx<T> as, cx<T> beta, cx<T> (&x)[5]) {
+  sym4_apply_prep<T>(sym4_prepare<T>(as, beta), x);
+}
+
+// x <- (n + nl) (1 + ss) x for the normalisation n (+ its FP32 rounding nl) and a phase
+// factor 1 + ss: n x + (nl + n ss) x with the small product formed first (inc_apply).
+template <typename T>
+__device__ __forceinline__ void scale_phase(T n, T nl, cx<T> ss, cx<T> (&x)[5]) {
+  const cx<T> c = mk<T>(nl + n * ss.re, n * ss.im);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const cx<T> d = c * x[i];
+    x[i] = mk<T>(fma(n, x[i].re, d.re), fma(n, x[i].im, d.im));
+  }
 }
 
 // cos(x) - 1 and sin(x)/x without cancellation or division by zero.
@@ -630,37 +645,37 @@ __device__ __forceinline__ void cosm1_sinc(T x, T& cm1, T& sc) {
   }
 }
 
-// exp(-i phi) - 1 = (cos phi - 1) - i sin phi for an FP64 phase, both parts to full
-// FP64 accuracy without cancellation and without a general-range sin/cos: phi is
-// reduced mod 2 pi to r in [-pi, pi] (two-part 2 pi), q = r/4 lies in [-pi/4, pi/4],
-// where the Taylor series of sin q (to q^15) and cos q (to q^16) truncate below
-// 5e-17; then sin(r/2) = 2 sin q cos q gives
+// exp(-i phi) - 1 = (cos phi - 1) - i sin phi for an FP64 phase, both parts without
+// cancellation and without a general-range sin/cos: phi is reduced mod 2 pi to r in
+// [-pi, pi] (two-part 2 pi), q = r/4 lies in [-pi/4, pi/4], where the Taylor series of
+// sin q and cos q are summed to q^15 and q^16 (truncated below 5e-17), or, where the
+// result is rounded to FP32, to q^11 and q^12 (below 1e-11); then sin(r/2) = 2 sin q cos q
+// gives
 //   cos phi - 1 = -2 sin^2(r/2) = -8 sin^2 q cos^2 q,
 //   sin phi = 2 sin(r/2) cos(r/2) = 4 sin q cos q (1 - 2 sin^2 q).
+template <typename T>
 __device__ __forceinline__ void phase_inc(double phi, double& cm1, double& sn) {
   const double k = rint(phi * 0.15915494309189533576888376337251437);
   double r = fma(-k, 6.283185307179586231995926937088370323, phi);
   r = fma(-k, 2.449293598294706e-16, r);
   const double q = 0.25 * r, q2 = q * q;
-  const double sq =
-      q * fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, -7.647163731819816475901131985788e-13,
-                                                                 1.605904383682161459939237717015e-10),
-                                                         -2.505210838544171877505210838544e-8),
-                                                 2.755731922398589065255731922399e-6),
-                                         -1.984126984126984126984126984127e-4),
-                                 8.333333333333333333333333333333e-3),
-                         -1.666666666666666666666666666667e-1),
-              1.0);
-  const double cq =
-      fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, 4.779477332387385297438207491118e-14,
-                                                                 -1.147074559772972471385169797868e-11),
-                                                         2.087675698786809897921009032120e-9),
-                                                 -2.755731922398589065255731922399e-7),
-                                         2.480158730158730158730158730159e-5),
-                                 -1.388888888888888888888888888889e-3),
-                         4.166666666666666666666666666667e-2),
-                 -0.5),
-          1.0);
+  double sp = -2.505210838544171877505210838544e-8;   // -1/11!
+  double cp = 2.087675698786809897921009032120e-9;    // 1/12!
+  if constexpr (sizeof(T) == 8) {
+    sp = fma(q2, fma(q2, -7.647163731819816475901131985788e-13, 1.605904383682161459939237717015e-10), sp);
+    cp = fma(q2, fma(q2, 4.779477332387385297438207491118e-14, -1.147074559772972471385169797868e-11), cp);
+  }
+  const double sq = q * fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, sp, 2.755731922398589065255731922399e-6),
+                                                    -1.984126984126984126984126984127e-4),
+                                            8.333333333333333333333333333333e-3),
+                                    -1.666666666666666666666666666667e-1),
+                            1.0);
+  const double cq = fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, cp, -2.755731922398589065255731922399e-7),
+                                                        2.480158730158730158730158730159e-5),
+                                                -1.388888888888888888888888888889e-3),
+                                        4.166666666666666666666666666667e-2),
+                                -0.5),
+                        1.0);
   const double sc = sq * cq;
   cm1 = -8.0 * sc * sc;
   sn = 4.0 * sc * fma(-2.0 * sq, sq, 1.0);
@@ -674,7 +689,7 @@ __device__ __forceinline__ void phase_inc(double phi, double& cm1, double& sn) {
 // sym4 of exp(-i c1 d F.sigma/2): alpha = cos(kappa/2) - i s F_z,
 // beta = -i s F_-, s = sin(kappa/2)/|F| = (c1 d/2) sinc(kappa/2), kappa = c1 d |F|.
 // The scalar phase is evaluated in FP64 (argument, its reduction mod 2 pi, and
-// exp(-i phi) - 1) and folded into the rotation's diagonal.  Every factor enters
+// exp(-i phi) - 1) and folded into the coefficients of b.  Every factor enters
 // in increment form (cos - 1, exp(-i phi) - 1, ...).
 // ---------------------------------------------------------------------------
 struct NLCoef {
@@ -691,9 +706,11 @@ __device__ __forceinline__ void nl_point(cx<T> (&p)[5], double V, const NLCoef& 
   const T rho = n0 + n1 + n2 + n3 + n4;
   const T Fz = T(2) * (n0 - n4) + (n1 - n3);
   // F_+ = 2 (conj(psi2) psi1 + conj(psi-1) psi-2) + sqrt6 (conj(psi1) psi0 + conj(psi0) psi-1)
-  const cx<T> Fp = T(2) * (cmulc(p[0], p[1]) + cmulc(p[3], p[4])) + r6 * (cmulc(p[1], p[2]) + cmulc(p[2], p[3]));
+  const cx<T> f1 = cfmac(p[3], p[4], cmulc(p[0], p[1])), f2 = cfmac(p[2], p[3], cmulc(p[1], p[2]));
+  const cx<T> Fp = mk<T>(T(2) * f1.re + r6 * f2.re, T(2) * f1.im + r6 * f2.im);
   // A00 = (2 psi2 psi-2 - 2 psi1 psi-1 + psi0^2)/sqrt5
-  const cx<T> A00 = r5i * (T(2) * (p[0] * p[4] - p[1] * p[3]) + p[2] * p[2]);
+  const cx<T> a1 = cfnma(p[1], p[3], p[0] * p[4]), a2 = p[2] * p[2];
+  const cx<T> A00 = r5i * mk<T>(T(2) * a1.re + a2.re, T(2) * a1.im + a2.im);
   const T rho5 = rho * T(0.2);
   T S2 = rho5 * rho5 - norm2(A00) * T(0.2);
   S2 = S2 > T(0) ? S2 : T(0);
@@ -702,18 +719,26 @@ __device__ __forceinline__ void nl_point(cx<T> (&p)[5], double V, const NLCoef& 
   T cm1, snc;
   cosm1_sinc<T>(c2d * S, cm1, snc);
   const T snS = c2d * snc;  // sin(c2 S d) / S
+  // scalar phase exp(-i phi) - 1, phi = d [V + (c0 + c2/5) rho], in FP64
+  double pcm1, psn;
+  phase_inc<T>(K.d * (V + K.c0p * (double)rho), pcm1, psn);
+  const cx<T> phs = mk<T>((T)pcm1, (T)(-psn));  // exp(-i phi) - 1
   // b = psi + (cos - 1) psi + i snS (rho/5 psi - A00 (A conj psi)_i),
   // (A conj psi)_i = (-1)^i conj(psi_(4-i)) / sqrt5, i.e.
-  // b_i = psi_i + k1 psi_i - k2 (-1)^i conj(psi_(4-i)) with k1 = (cos - 1) + i snS rho/5
-  // and k2 = i snS A00 / sqrt5
+  // b_i = (1 + k1) psi_i - k2 (-1)^i conj(psi_(4-i)) with k1 = (cos - 1) + i snS rho/5
+  // and k2 = i snS A00 / sqrt5; with the scalar phase: K1 = k1 + phs + k1 phs for k1 and
+  // K2 = k2 + k2 phs for k2
   const cx<T> k1 = mk<T>(cm1, snS * rho5);
   const cx<T> k2 = mul_i((snS * r5i) * A00);
+  const cx<T> K1 = cfma(k1, phs, k1 + phs);
+  const cx<T> K2 = cfma(k2, phs, k2);
   cx<T> b[5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    cx<T> ab = conj(p[4 - i]);
-    if (i & 1) ab = mk<T>(-ab.re, -ab.im);
-    b[i] = p[i] + (k1 * p[i] - k2 * ab);
+    const cx<T> ab = conj(p[4 - i]);
+    const cx<T> kp = K1 * p[i];
+    const cx<T> e = (i & 1) ? cfma(K2, ab, kp) : cfnma(K2, ab, kp);
+    b[i] = p[i] + e;
   }
   // spin rotation: alpha - 1 = (cos(kappa/2) - 1) - i s F_z, beta = -i s F_-
   const T Fabs = sqrt_nn(norm2(Fp) + Fz * Fz);
@@ -723,11 +748,7 @@ __device__ __forceinline__ void nl_point(cx<T> (&p)[5], double V, const NLCoef& 
   const T s = hc1d * skc;  // sin(kappa/2)/|F|
   const cx<T> as = mk<T>(ckm1, -s * Fz);
   const cx<T> beta = mk<T>(-s * Fp.im, -s * Fp.re);
-  // scalar phase exp(-i phi) - 1, phi = d [V + (c0 + c2/5) rho], in FP64
-  double pcm1, psn;
-  phase_inc(K.d * (V + K.c0p * (double)rho), pcm1, psn);
-  const cx<T> phs = mk<T>((T)pcm1, (T)(-psn));  // exp(-i phi) - 1
-  sym4_apply_inc<T>(as, beta, phs, b);
+  sym4_apply_inc<T>(as, beta, b);
 #pragma unroll
   for (int i = 0; i < 5; ++i) p[i] = b[i];
 }
@@ -761,8 +782,10 @@ __device__ __forceinline__ void nl_point_adj(const cx<T> (&p)[5], cx<T> (&g)[5],
   const T n0 = norm2(p[0]), n1 = norm2(p[1]), n2 = norm2(p[2]), n3 = norm2(p[3]), n4 = norm2(p[4]);
   const T rho = n0 + n1 + n2 + n3 + n4;
   const T Fz = T(2) * (n0 - n4) + (n1 - n3);
-  const cx<T> Fp = T(2) * (cmulc(p[0], p[1]) + cmulc(p[3], p[4])) + r6 * (cmulc(p[1], p[2]) + cmulc(p[2], p[3]));
-  const cx<T> A00 = r5i * (T(2) * (p[0] * p[4] - p[1] * p[3]) + p[2] * p[2]);
+  const cx<T> f1 = cfmac(p[3], p[4], cmulc(p[0], p[1])), f2 = cfmac(p[2], p[3], cmulc(p[1], p[2]));
+  const cx<T> Fp = mk<T>(T(2) * f1.re + r6 * f2.re, T(2) * f1.im + r6 * f2.im);
+  const cx<T> a1 = cfnma(p[1], p[3], p[0] * p[4]), a2 = p[2] * p[2];
+  const cx<T> A00 = r5i * mk<T>(T(2) * a1.re + a2.re, T(2) * a1.im + a2.im);
   const T rho5 = rho * T(0.2);
   T S2 = rho5 * rho5 - norm2(A00) * T(0.2);
   S2 = S2 > T(0) ? S2 : T(0);
@@ -791,10 +814,12 @@ __device__ __forceinline__ void nl_point_adj(const cx<T> (&p)[5], cx<T> (&g)[5],
   const cx<T> as = mk<T>(ckm1, -sr * Fz);
   const cx<T> beta = mk<T>(-sr * Fp.im, -sr * Fp.re);
   double pcm1, psn;
-  phase_inc(K.d * (V + K.c0p * (double)rho), pcm1, psn);
-  const cx<T> phs = mk<T>((T)pcm1, (T)(-psn));
+  phase_inc<T>(K.d * (V + K.c0p * (double)rho), pcm1, psn);
+  const cx<T> phc = mk<T>((T)pcm1, (T)psn);  // exp(i phi) - 1
   // h = exp(i phi) R^H g', in place
-  sym4_apply_inc<T>(conj(as), mk<T>(-beta.re, -beta.im), conj(phs), g);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) g[i] = inc_apply(phc, g[i]);
+  sym4_apply_inc<T>(conj(as), mk<T>(-beta.re, -beta.im), g);
   // q_phi = Im(h^H b); m_a = Im(h^H f_a b)
   double qphi = 0.0;
 #pragma unroll

@@ -345,17 +345,12 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
         const cx<T> beta = mk<T>(S * ga * nup, -S * ga * nuq);
         const cx<T> ss = ka + kl1 + ka * kl1;  // kinetic phase - 1
         cx<T> p[5];
-        if (norm_lo == T(0)) {
 #pragma unroll
-          for (int cc = 0; cc < 5; ++cc) p[cc] = norm * lx[pt * 5 + cc];
-        } else {
-#pragma unroll
-          for (int cc = 0; cc < 5; ++cc)
-            p[cc] = mk<T>(kmul<T>(norm, norm_lo, lx[pt * 5 + cc].re), kmul<T>(norm, norm_lo, lx[pt * 5 + cc].im));
-        }
+        for (int cc = 0; cc < 5; ++cc) p[cc] = lx[pt * 5 + cc];
+        scale_phase<T>(norm, norm_lo, KIND == C_ADJ ? conj(ss) : ss, p);
         if constexpr (KIND == C_ADJ) {
           // P^H = P(-d): same (C - 1), S -> -S, conjugate kinetic phase
-          sym4_apply_inc<T>(conj(as), mk<T>(-beta.re, -beta.im), conj(ss), p);
+          sym4_apply_inc<T>(conj(as), mk<T>(-beta.re, -beta.im), p);
           if (kx0 + pc < a.ncols) {
             // m_a = -d Im(L^H f_a H), L = P^H L'/N^d (p), H the stored forward input
             const cx<T>* fw = reinterpret_cast<const cx<T>*>(a.fwd) + o * (int)a.outer_stride + kx * 5 + kl * (int)a.stride;
@@ -394,7 +389,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
             gacc[1] += -Dz;                     // dn/dOmega = (0, 0, -1)
           }
         } else {
-          sym4_apply_inc<T>(as, beta, ss, p);
+          sym4_apply_inc<T>(as, beta, p);
         }
 #pragma unroll
         for (int cc = 0; cc < 5; ++cc) lx[pt * 5 + cc] = p[cc];
