@@ -628,23 +628,6 @@ __device__ __forceinline__ void scale_phase(T n, T nl, cx<T> ss, cx<T> (&x)[5]) 
   }
 }
 
-// cos(x) - 1 and sin(x)/x without cancellation or division by zero.
-template <typename T>
-__device__ __forceinline__ void cosm1_sinc(T x, T& cm1, T& sc) {
-  const T x2 = x * x;
-  const T small = sizeof(T) == 4 ? T(1e-2) : T(1e-4);
-  if (fabs(x) < small) {
-    sc = T(1) - x2 * (T(1) / T(6)) * (T(1) - x2 * T(0.05));
-    cm1 = -x2 * T(0.5) * (T(1) - x2 * (T(1) / T(12)));
-  } else {
-    T s, c, sh, ch;
-    if constexpr (sizeof(T) == 4) { sincosf(x, &s, &c); sincosf(T(0.5) * x, &sh, &ch); }
-    else { sincos(x, &s, &c); sincos(T(0.5) * x, &sh, &ch); }
-    sc = s / x;
-    cm1 = T(-2) * sh * sh;
-  }
-}
-
 // exp(-i phi) - 1 = (cos phi - 1) - i sin phi for an FP64 phase, both parts without
 // cancellation and without a general-range sin/cos: phi is reduced mod 2 pi to r in
 // [-pi, pi] (two-part 2 pi), q = r/4 lies in [-pi/4, pi/4], where the Taylor series of
@@ -679,6 +662,29 @@ __device__ __forceinline__ void phase_inc(double phi, double& cm1, double& sn) {
   const double sc = sq * cq;
   cm1 = -8.0 * sc * sc;
   sn = 4.0 * sc * fma(-2.0 * sq, sq, 1.0);
+}
+
+// cos(x) - 1 and sin(x)/x without cancellation or division by zero.  The angles of a
+// substep (c d |F|, c d S) are small nearly everywhere: two terms of the series (four in
+// FP64); the others through phase_inc (the library's sin/cos, two calls with their
+// large-argument reductions, made up half of the x-pass's code).
+template <typename T>
+__device__ __forceinline__ void cosm1_sinc(T x, T& cm1, T& sc) {
+  const T x2 = x * x;
+  if (x2 <= T(1e-4)) {
+    if constexpr (sizeof(T) == 4) {
+      sc = fma(x2, fma(x2, T(1.0 / 120), T(-1.0 / 6)), T(1));
+      cm1 = x2 * fma(x2, T(1.0 / 24), T(-0.5));
+    } else {
+      sc = fma(x2, fma(x2, fma(x2, T(-1.0 / 5040), T(1.0 / 120)), T(-1.0 / 6)), T(1));
+      cm1 = x2 * fma(x2, fma(x2, fma(x2, T(1.0 / 40320), T(-1.0 / 720)), T(1.0 / 24)), T(-0.5));
+    }
+  } else {
+    double c, s;
+    phase_inc<T>((double)x, c, s);
+    cm1 = (T)c;
+    sc = (T)(s / (double)x);
+  }
 }
 
 // ---------------------------------------------------------------------------
