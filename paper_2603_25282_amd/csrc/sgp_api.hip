@@ -89,6 +89,10 @@ struct sgp_ctx {
   size_t ws_bytes = 0;
   size_t total = 0;
   size_t off_tw[3][2];
+  // 3D: width of the line kernel of the axis's pass (x: X kinds, y: C_PROP, z: C_KIN), 0 =
+  // none, and its twiddle tables
+  int line_e[3] = {0, 0, 0};
+  size_t off_twl[3][2];
   size_t off_cs[4];      // (C - 1, S) table per distinct linear substep length
   size_t off_kin[4][3];
   size_t off_clock;
@@ -171,29 +175,36 @@ struct TS4 {
   }
 };
 
+// Twiddle tables of plan width e of an axis at workspace offsets off[2].
 template <typename T>
-hipError_t upload_twiddles(sgp_ctx* c) {
-  for (int ax = 0; ax < c->g.dim; ++ax) {
-    for (int dir = 0; dir < 2; ++dir) {
-      auto tab = twiddle_table(plan_radices(c->g.n[ax], c->elems(ax), dir == 0));
-      // each twiddle as a (hi, lo) pair: hi = w rounded to T, lo = (w - hi) rounded
-      std::vector<T> buf(4 * tab.size() + 4);
-      for (size_t i = 0; i < tab.size(); ++i) {
-        T hr = (T)tab[i].real(), hi = (T)tab[i].imag();
-        buf[4 * i] = hr;
-        buf[4 * i + 1] = hi;
-        buf[4 * i + 2] = (T)(tab[i].real() - (double)hr);
-        buf[4 * i + 3] = (T)(tab[i].imag() - (double)hi);
-      }
-      if (tab.empty()) continue;
-      hipError_t e = hipMemcpyAsync(c->at(c->off_tw[ax][dir]), buf.data(), sizeof(T) * 4 * tab.size(),
-                                    hipMemcpyHostToDevice, c->st);
-      if (e != hipSuccess) return e;
-      e = hipStreamSynchronize(c->st);
-      if (e != hipSuccess) return e;
+hipError_t upload_tables(sgp_ctx* c, int ax, int e, const size_t* off) {
+  for (int dir = 0; dir < 2; ++dir) {
+    auto tab = twiddle_table(plan_radices(c->g.n[ax], e, dir == 0));
+    // each twiddle as a (hi, lo) pair: hi = w rounded to T, lo = (w - hi) rounded
+    std::vector<T> buf(4 * tab.size() + 4);
+    for (size_t i = 0; i < tab.size(); ++i) {
+      T hr = (T)tab[i].real(), hi = (T)tab[i].imag();
+      buf[4 * i] = hr;
+      buf[4 * i + 1] = hi;
+      buf[4 * i + 2] = (T)(tab[i].real() - (double)hr);
+      buf[4 * i + 3] = (T)(tab[i].imag() - (double)hi);
     }
+    if (tab.empty()) continue;
+    hipError_t r = hipMemcpyAsync(c->at(off[dir]), buf.data(), sizeof(T) * 4 * tab.size(), hipMemcpyHostToDevice, c->st);
+    if (r == hipSuccess) r = hipStreamSynchronize(c->st);
+    if (r != hipSuccess) return r;
   }
   return hipSuccess;
+}
+
+template <typename T>
+hipError_t upload_twiddles(sgp_ctx* c) {
+  hipError_t r = hipSuccess;
+  for (int ax = 0; ax < c->g.dim && r == hipSuccess; ++ax) {
+    r = upload_tables<T>(c, ax, c->elems(ax), c->off_tw[ax]);
+    if (r == hipSuccess && c->line_e[ax]) r = upload_tables<T>(c, ax, c->line_e[ax], c->off_twl[ax]);
+  }
+  return r;
 }
 
 // Fields shared by every pass of a context.
@@ -263,17 +274,28 @@ void propagator_tables(const sgp_ctx* c, int table, int axis, PassArgs& a) {
 // with z-slabs no slab's y-pass moves the clock under another slab's X-pass.
 int advances_clock(const sgp_ctx* c, int kind) { return kind == (c->g.dim == 2 ? C_PROP : C_KIN); }
 
+// Launch a pass along `axis`: the line kernel where the context has one for it, else the
+// component-split kernel of the axis's plan.
+template <typename T>
+hipError_t launch_axis(sgp_ctx* c, int kind, int axis, void* psi, PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
+  const int n = c->g.n[axis];
+  const bool line = c->line_e[axis] && line_elems(kind, n, (int)c->esize, c->npts());
+  const size_t* tw = line ? c->off_twl[axis] : c->off_tw[axis];
+  a.tw_fwd = c->at(tw[0]);
+  a.tw_inv = c->at(tw[1]);
+  return line ? launch_line<T>(kind, psi, a, n, c->line_e[axis], st, ev)
+              : launch_pass<T>(kind, psi, a, n, c->elems(axis), st, ev);
+}
+
 template <typename T>
 hipError_t run_xpass(sgp_ctx* c, hipStream_t st, int mode, void* psi, double d, int clock_mode, double s_arg,
                      const hipEvent_t* ev = nullptr) {
   PassArgs a = base_args(c);
-  a.tw_fwd = c->at(c->off_tw[0][0]);
-  a.tw_inv = c->at(c->off_tw[0][1]);
   a.d = d;
   host_clock(a, s_arg);
   a.clock_mode = clock_mode;
   if (!ev) ev = timing_events(c, mode == X_MID ? 0 : -1);
-  return launch_pass<T>(mode, psi, a, c->g.n[0], c->elems(0), st, ev);
+  return launch_axis<T>(c, mode, 0, psi, a, st, ev);
 }
 
 template <typename T>
@@ -285,7 +307,7 @@ hipError_t run_colpass(sgp_ctx* c, hipStream_t st, int mode, int axis, void* psi
   a.d = d;
   a.advance_clock = advances_clock(c, mode);
   if (!ev) ev = timing_events(c, axis);
-  return launch_pass<T>(mode, psi, a, c->g.n[axis], c->elems(axis), st, ev);
+  return launch_axis<T>(c, mode, axis, psi, a, st, ev);
 }
 
 // Store-mode and adjoint variants of the passes.
@@ -293,15 +315,13 @@ template <typename T>
 hipError_t run_xpass_ex(sgp_ctx* c, int kind, void* psi, double d, int clock_mode, double s_arg, void* store,
                         const void* fwd) {
   PassArgs a = base_args(c);
-  a.tw_fwd = c->at(c->off_tw[0][0]);
-  a.tw_inv = c->at(c->off_tw[0][1]);
   a.d = d;
   host_clock(a, s_arg);
   a.clock_mode = clock_mode;
   a.store = store;
   a.fwd = fwd;
   a.gacc = (double*)c->at(c->off_gacc);
-  return launch_pass<T>(kind, psi, a, c->g.n[0], c->elems(0), c->st);
+  return launch_axis<T>(c, kind, 0, psi, a, c->st, nullptr);
 }
 
 template <typename T>
@@ -316,7 +336,7 @@ hipError_t run_colpass_ex(sgp_ctx* c, int kind, int axis, void* psi, int table, 
   a.store = store;
   a.fwd = fwd;
   a.gacc = (double*)c->at(c->off_gacc);
-  return launch_pass<T>(kind, psi, a, c->g.n[axis], c->elems(axis), c->st);
+  return launch_axis<T>(c, kind, axis, psi, a, c->st, nullptr);
 }
 
 // One exact linear substep on x-transformed data: the y-pass (FFT along y, spin part
@@ -428,17 +448,15 @@ hipError_t run_slab_pass(sgp_ctx* c, hipStream_t st, int kind, void* psi, int z0
   void* p = (char*)psi + (size_t)z0 * ny * nx * 5 * 2 * c->esize;
   a.d = d;
   if (kind == X_MID) {
-    a.tw_fwd = c->at(c->off_tw[0][0]);
-    a.tw_inv = c->at(c->off_tw[0][1]);
     a.clock_mode = CLOCK_DEVICE;
     a.nlines = (long)(z1 - z0) * ny;
     a.z0 = z0;
-    return launch_pass<T>(kind, p, a, nx, c->elems(0), st, nullptr);
+    return launch_axis<T>(c, kind, 0, p, a, st, nullptr);
   }
   column_geometry(c, 1, a);
   propagator_tables(c, table, 1, a);
   a.nouter = z1 - z0;
-  return launch_pass<T>(kind, p, a, ny, c->elems(1), st, nullptr);
+  return launch_axis<T>(c, kind, 1, p, a, st, nullptr);
 }
 
 // enqueue_body with the z-local passes in z-slabs (3D, split 0): the x-pass and the next
@@ -1151,6 +1169,16 @@ int sgp_create(const sgp_grid* grid, const sgp_params* params, int dtype, void* 
           most = std::max(most, twiddle_table(plan_radices(c->g.n[ax], e, dir == 0)).size());
       if (ax < c->g.dim) off += align256(4 * c->esize * (most + 1));
     }
+  if (c->g.dim == 3) {
+    const int kind[3] = {X_MID, C_PROP, C_KIN};
+    for (int ax = 0; ax < 3; ++ax) {
+      c->line_e[ax] = line_elems(kind[ax], c->g.n[ax], (int)c->esize, c->npts());
+      for (int dir = 0; dir < 2 && c->line_e[ax]; ++dir) {
+        c->off_twl[ax][dir] = off;
+        off += align256(4 * c->esize * (twiddle_table(plan_radices(c->g.n[ax], c->line_e[ax], dir == 0)).size() + 1));
+      }
+    }
+  }
   const size_t nxy = (size_t)c->g.n[0] * c->g.n[1];
   for (int k = 0; k < 4; ++k) {
     c->off_cs[k] = off;

@@ -31,6 +31,24 @@ hipError_t launch_pass(int kind, void* psi, const PassArgs& a, int n, int e, hip
   }
 }
 
+#define SGP_EXTERN_L(TT, EE) \
+  extern template hipError_t launch_line_e<TT, EE>(int, void*, const PassArgs&, int, hipStream_t, const hipEvent_t*);
+SGP_EXTERN_L(float, 4) SGP_EXTERN_L(float, 8) SGP_EXTERN_L(float, 12) SGP_EXTERN_L(double, 4) SGP_EXTERN_L(double, 8)
+#undef SGP_EXTERN_L
+
+template <typename T>
+hipError_t launch_line(int kind, void* psi, const PassArgs& a, int n, int e, hipStream_t st, const hipEvent_t* ev) {
+  if (!line_ok(n, e, (int)sizeof(T))) return hipErrorInvalidValue;
+  switch (e) {
+    case 4: return launch_line_e<T, 4>(kind, psi, a, n, st, ev);
+    case 8: return launch_line_e<T, 8>(kind, psi, a, n, st, ev);
+    case 12:
+      if constexpr (sizeof(T) == 4) return launch_line_e<T, 12>(kind, psi, a, n, st, ev);
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <typename T>
 hipError_t launch_obs(int kind, const void* psi, const PassArgs& a, int n, int e, double* part, hipStream_t st) {
   if (!plan_ok(n, e, (int)sizeof(T))) return hipErrorInvalidValue;
@@ -103,6 +121,8 @@ hipError_t launch_pass_batched(int kind, int e, const void* items, const void* a
 
 template hipError_t launch_pass_batched<float>(int, int, const void*, const void*, long, int, hipStream_t);
 template hipError_t launch_pass_batched<double>(int, int, const void*, const void*, long, int, hipStream_t);
+template hipError_t launch_line<float>(int, void*, const PassArgs&, int, int, hipStream_t, const hipEvent_t*);
+template hipError_t launch_line<double>(int, void*, const PassArgs&, int, int, hipStream_t, const hipEvent_t*);
 template hipError_t launch_pass<float>(int, void*, const PassArgs&, int, int, hipStream_t, const hipEvent_t*);
 template hipError_t launch_pass<double>(int, void*, const PassArgs&, int, int, hipStream_t, const hipEvent_t*);
 template hipError_t launch_obs<float>(int, const void*, const PassArgs&, int, int, double*, hipStream_t);

@@ -95,7 +95,41 @@ constexpr int obs_lines_per_block(int n, int e) {
   return w;
 }
 
+// The line kernels (sgp_lines.hpp: five components per thread): points per thread of a
+// pass over lines of length n of a 3D grid of npts points, or 0 where the component-split
+// kernel of the axis's plan runs.  Measured (in-step, complex64 unless noted, component-
+// split with its best width against the line kernel):
+//   * small grids have too few lines: 64^3 x 11.9 against 14.9 us, 128x64x64 17.9 against
+//     20.5 (complex128 39.7 against 27.5); 128^3: x 57.7 against 51.0, y 46.1 against 44.1.
+//   * powers of two up to 256 run E = 4 (radix 4, 5 wavefronts per SIMD): with E = 8 the
+//     x-pass takes 52.9 and the y-pass 47.5 at 128^3 (3 wavefronts per SIMD).  512: E = 8,
+//     the widest line that fits a wavefront: x 70.2 against 55.3.
+//   * 3 * 2^k: E = 12 (192^3: x 222 against 179, y 217 against 172, z 157 against 154).
+//   * z-pass (three transforms' worth of traffic and little arithmetic): the
+//     component-split kernel streams faster (128^3 33.1 against 38.0) up to the Infinity
+//     Cache's size; beyond it the line kernel (256^3 355 against 301), and for 384, 768
+//     (47.8 against 40.9).
+//   * complex128: E = 4 (128x128x64: x 48.5 against 39.0, y 62.5 against 43.1, z 47.5
+//     against 37.8), z-lines of 64 stay (28.7 against 32.2); 512: E = 8 (z 53.5 against
+//     40.4); 3 * 2^k would need 240 registers of state.
+constexpr long line_points_min(int esize) { return esize == 4 ? 1L << 20 : 1L << 19; }
+constexpr int line_elems(int kind, int n, int esize, long npts) {
+  const bool z = kind == C_KIN, p2 = n == 64 || n == 128 || n == 256;
+  if (npts < line_points_min(esize) || !(kind == X_FIRST || kind == X_MID || kind == X_LAST || kind == C_PROP || z)) return 0;
+  if (esize == 8) return p2 ? (z && n == 64 ? 0 : 4) : n == 512 ? 8 : 0;
+  if (z) return n == 256 && npts >= (1L << 23) ? 8 : (n == 384 || n == 768) ? 12 : 0;
+  return p2 ? 4 : n == 512 ? 8 : (n == 192 || n == 384 || n == 768) ? 12 : 0;
+}
+// (n, e) pairs with a compiled line kernel
+constexpr bool line_ok(int n, int e, int esize) {
+  return e == 4 ? (n == 64 || n == 128 || n == 256) : e == 8 ? (n == 512 || (n == 256 && esize == 4))
+                : (e == 12 && esize == 4 && (n == 192 || n == 384 || n == 768));
+}
+
 // ev: null, or a start / end event pair stamped by the kernel's dispatch
+template <typename T>
+hipError_t launch_line(int kind, void* psi, const PassArgs& a, int n, int e, hipStream_t st,
+                       const hipEvent_t* ev = nullptr);
 template <typename T>
 hipError_t launch_pass(int kind, void* psi, const PassArgs& a, int n, int e, hipStream_t st,
                        const hipEvent_t* ev = nullptr);
@@ -119,6 +153,8 @@ hipError_t launch_pass_batched(int kind, int e, const void* items, const void* a
 // per-plan-width launchers, each (T, E) compiled in its own translation unit
 template <typename T, int E>
 hipError_t launch_pass_e(int kind, void* psi, const PassArgs& a, int n, hipStream_t st, const hipEvent_t* ev);
+template <typename T, int E>
+hipError_t launch_line_e(int kind, void* psi, const PassArgs& a, int n, hipStream_t st, const hipEvent_t* ev);
 template <typename T, int E>
 hipError_t launch_obs_e(int kind, const void* psi, const PassArgs& a, int n, double* part, hipStream_t st);
 

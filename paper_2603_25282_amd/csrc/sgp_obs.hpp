@@ -1,7 +1,7 @@
 // Observables and diagnostics kernels (Sec. 2) and their per-plan launchers, in a
 // header of their own: the pass kernels of sgp_passes.hpp do not depend on it.
 #pragma once
-#include "sgp_passes.hpp"
+#include "sgp_launch.hpp"
 
 namespace sgp {
 

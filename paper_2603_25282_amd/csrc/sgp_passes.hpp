@@ -27,8 +27,6 @@
 // (components innermost), every thread updates whole points from the tile, and
 // the FFT threads read their elements back.
 #pragma once
-#include <hip/hip_ext.h>
-
 #include "sgp_device.hpp"
 #include "sgp_kernels.hpp"
 
@@ -68,6 +66,47 @@ __device__ __forceinline__ void advance_clock(const PassArgs& a) {
   a.clock[0] = s1;
   a.clock[1] = cn;
   a.clock[2] = sn;
+}
+
+// The trap at R(Omega s) x.
+__device__ __forceinline__ double trap_potential(const PassArgs& a, double ct, double st, double x, double y,
+                                                 double z) {
+  const double X = ct * x + st * y, Y = -st * x + ct * y;
+  return 0.5 * (a.g2[0] * X * X + a.g2[1] * Y * Y + a.g2[2] * z * z);
+}
+
+// Coefficients of the propagator that a column (kx) shares.
+template <typename T>
+struct PropCoef {
+  T Om, nup, ga, norm, norm_lo;
+  double nu_q;
+  int n_q;
+  __device__ __forceinline__ PropCoef(const PassArgs& a, int kx) {
+    const int px = kx < (int)a.ncols / 2 ? kx : kx - (int)a.ncols;
+    Om = T(a.Omega);
+    ga = T(a.gamma);
+    nup = T(px * a.nu_scale_a);
+    norm = T(a.norm);
+    // 1/N^d as a (hi, lo) pair: exact for powers of two, compensated otherwise
+    norm_lo = T(a.norm - (double)norm);
+    nu_q = a.nu_scale_q;
+    n_q = a.n_q;
+  }
+};
+
+// The propagator's in-plane part with 1/N^d at (kx, kl) from the table entry (C - 1, S)
+// and the kinetic increments along x and y.
+template <typename T>
+__device__ __forceinline__ void prop_point(const PropCoef<T>& P, int kl, T Cm1, T S, cx<T> ka, cx<T> kl1,
+                                           cx<T> (&p)[5]) {
+  const int pq = kl < P.n_q / 2 ? kl : kl - P.n_q;
+  const T nuq = T(pq * P.nu_q);
+  // alpha - 1 = (C - 1) - i S Omega; beta = i S gamma a = S gamma (nu_p - i nu_q)
+  const cx<T> as = mk<T>(Cm1, -S * P.Om);
+  const cx<T> beta = mk<T>(S * P.ga * P.nup, -S * P.ga * nuq);
+  const cx<T> ss = ka + kl1 + ka * kl1;  // kinetic phase - 1
+  scale_phase<T>(P.norm, P.norm_lo, ss, p);
+  sym4_apply_inc<T>(as, beta, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -280,8 +319,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
         const double x = -a.L[0] + j * a.h[0];
         const double y = -a.L[1] + iy * a.h[1];
         const double z = -a.L[2] + iz * a.h[2];
-        const double X = ct * x + st * y, Y = -st * x + ct * y;
-        const double V = 0.5 * (a.g2[0] * X * X + a.g2[1] * Y * Y + a.g2[2] * z * z);
+        const double V = trap_potential(a, ct, st, x, y, z);
         cx<T> p[5];
 #pragma unroll
         for (int cc = 0; cc < 5; ++cc) p[cc] = lx[pt * 5 + cc];
@@ -292,6 +330,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
 #pragma unroll
           for (int cc = 0; cc < 5; ++cc) q[cc] = fw[cc];
           // dV/dOmega = s (gx^2 - gy^2) X Y (trap at R(Omega s) x)
+          const double X = ct * x + st * y, Y = -st * x + ct * y;
           const double dVdO = a.s_arg * (a.g2[0] - a.g2[1]) * X * Y;
           double acc4[4] = {0.0, 0.0, 0.0, 0.0};
           nl_point_adj<T>(q, p, V, dVdO, K, acc4);
@@ -560,119 +599,6 @@ __global__ void k_build_kin(cx<T>* __restrict__ kin, int n, double L, double d) 
   const double sh = sin(0.5 * ph);
   kin[k].re = (T)(-2.0 * sh * sh);
   kin[k].im = (T)sin(ph);
-}
-
-
-// ---------------------------------------------------------------------------
-// Launch geometry of a register plan (N, E): TL = N/E threads per line and
-// component; W lines per block so that a block has 320 threads (W = 64/TL), or one
-// line of 5 TL threads when TL > 64.  Every instantiation of a plan (alone or in
-// an ensemble) uses this geometry, so its results do not depend on the caller.
-// ---------------------------------------------------------------------------
-template <int N, int E>
-struct Geo {
-  static constexpr int TL = N / E;
-  static constexpr int W = TL >= 64 ? 1 : 64 / TL;
-  static constexpr int NT = W * 5 * TL;
-};
-
-// Blocks of a pass with W lines per block.
-template <int W, int KIND>
-static long pass_blocks(const PassArgs& a) {
-  return KindInfo<KIND>::XL ? (a.nlines + W - 1) / W : ((a.ncols + W - 1) / W) * a.nouter;
-}
-
-// ev: null, or two events that the dispatch itself stamps with the kernel's start
-// and end (timing without marker packets between the kernels).
-template <typename T, int N, int E, int W, int KIND>
-static hipError_t pass_w(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
-  constexpr int NT = W * 5 * (N / E);
-  const long nblocks = pass_blocks<W, KIND>(a) + ((KIND == C_PROP || KIND == C_KIN) && a.advance_clock ? 1 : 0);
-  if (ev)
-    hipExtLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(NT), 0, st, ev[0], ev[1], 0, psi,
-                          a);
-  else
-    hipLaunchKernelGGL((k_pass<T, N, E, W, KIND>), dim3((unsigned)nblocks), dim3(NT), 0, st, psi, a);
-  return hipGetLastError();
-}
-
-// Lines per block: Geo's W, or one line where that would leave CUs without a block
-// (fewer than 256 blocks).  The arithmetic of a line does not depend on W; the adjoint
-// passes keep Geo's W, which fixes the grouping of their parameter partials.
-template <typename T, int N, int E, int KIND>
-static hipError_t pass_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
-  constexpr int W = Geo<N, E>::W;
-  if constexpr (W > 1 && !KindInfo<KIND>::ADJ) {
-    if (pass_blocks<W, KIND>(a) < 256) return pass_w<T, N, E, 1, KIND>(psi, a, st, ev);
-  }
-  return pass_w<T, N, E, W, KIND>(psi, a, st, ev);
-}
-
-template <typename T, int N, int E>
-static hipError_t pass_kind(int kind, cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
-  switch (kind) {
-    case X_FIRST: return pass_n<T, N, E, X_FIRST>(psi, a, st, ev);
-    case X_MID: return pass_n<T, N, E, X_MID>(psi, a, st, ev);
-    case X_LAST: return pass_n<T, N, E, X_LAST>(psi, a, st, ev);
-    case X_NLONLY: return pass_n<T, N, E, X_NLONLY>(psi, a, st, ev);
-    case C_PROP: return pass_n<T, N, E, C_PROP>(psi, a, st, ev);
-    case C_KIN: return pass_n<T, N, E, C_KIN>(psi, a, st, ev);
-    case XA_FIRST: return pass_n<T, N, E, XA_FIRST>(psi, a, st, ev);
-    case XA_MID: return pass_n<T, N, E, XA_MID>(psi, a, st, ev);
-    case XA_LAST: return pass_n<T, N, E, XA_LAST>(psi, a, st, ev);
-    case C_ADJ: return pass_n<T, N, E, C_ADJ>(psi, a, st, ev);
-    case X_SHEAR: return pass_n<T, N, E, X_SHEAR>(psi, a, st, ev);
-    case C_SHEAR: return pass_n<T, N, E, C_SHEAR>(psi, a, st, ev);
-    case X_FWD: return pass_n<T, N, E, X_FWD>(psi, a, st, ev);
-    case X_INV: return pass_n<T, N, E, X_INV>(psi, a, st, ev);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// All pass kernels of one register-plan width E (every supported
-// line length with that E).  Each (T, E) pair is compiled in its own translation
-// unit.
-#define SGP_FOR_PLAN_N(E, X)                                     \
-  X(16, E) X(32, E) X(64, E) X(128, E) X(192, E) X(256, E) X(384, E) X(512, E) X(768, E)
-
-template <typename T, int E>
-hipError_t launch_pass_e(int kind, void* psi, const PassArgs& a, int n, hipStream_t st, const hipEvent_t* ev) {
-  cx<T>* p = reinterpret_cast<cx<T>*>(psi);
-#define SGP_CASE(NN, EE) \
-  case NN:               \
-    if constexpr (plan_ok(NN, EE, (int)sizeof(T))) return pass_kind<T, NN, EE>(kind, p, a, st, ev); \
-    break;
-  switch (n) { SGP_FOR_PLAN_N(E, SGP_CASE) default: break; }
-#undef SGP_CASE
-  return hipErrorInvalidValue;
-}
-
-// Batched passes of one plan width (compiled with that width's unit).
-template <typename T, int E, int NMAX>
-static hipError_t launch_batched_nmax(int kind, const int2* it, const PassArgs* ar, long nitems, hipStream_t st) {
-  dim3 g((unsigned)nitems), b(320);
-  switch (kind) {
-    case X_FIRST: hipLaunchKernelGGL((k_pass_batched<T, X_FIRST, E, NMAX>), g, b, 0, st, it, ar); break;
-    case X_MID: hipLaunchKernelGGL((k_pass_batched<T, X_MID, E, NMAX>), g, b, 0, st, it, ar); break;
-    case X_LAST: hipLaunchKernelGGL((k_pass_batched<T, X_LAST, E, NMAX>), g, b, 0, st, it, ar); break;
-    case C_PROP: hipLaunchKernelGGL((k_pass_batched<T, C_PROP, E, NMAX>), g, b, 0, st, it, ar); break;
-    case XA_FIRST: hipLaunchKernelGGL((k_pass_batched<T, XA_FIRST, E, NMAX>), g, b, 0, st, it, ar); break;
-    case XA_MID: hipLaunchKernelGGL((k_pass_batched<T, XA_MID, E, NMAX>), g, b, 0, st, it, ar); break;
-    case XA_LAST: hipLaunchKernelGGL((k_pass_batched<T, XA_LAST, E, NMAX>), g, b, 0, st, it, ar); break;
-    case C_ADJ: hipLaunchKernelGGL((k_pass_batched<T, C_ADJ, E, NMAX>), g, b, 0, st, it, ar); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-// nmax: the longest line among the launch's instances
-template <typename T, int E>
-hipError_t launch_batched_e(int kind, const int2* it, const PassArgs* ar, long nitems, int nmax, hipStream_t st) {
-  if constexpr (E == 12 || E == 24) {
-    if (nmax > 512) return launch_batched_nmax<T, E, 768>(kind, it, ar, nitems, st);
-  }
-  if (nmax > 512) return hipErrorInvalidValue;
-  return launch_batched_nmax<T, E, 512>(kind, it, ar, nitems, st);
 }
 
 }  // namespace sgp
