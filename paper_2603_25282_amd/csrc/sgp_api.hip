@@ -118,12 +118,18 @@ struct sgp_ctx {
   std::string err;
 
   // replay of the periodic part of sgp_step: graphs of 2^k whole steps
-  // (k = 0..kGraphLevels-1), all captured together for the state pointer gpsi, so
-  // that any number of body steps replays from graphs (its binary digits)
+  // (k = 0..kGraphLevels-1) for the state pointer gpsi, each captured when first needed,
+  // so that any number of body steps replays from graphs (its binary digits).  A state
+  // buffer is captured from its second call in a row (seen) or for kGraphAtOnce body
+  // steps and more: the launches of a short first call cost the GPU the same time one by
+  // one (64^2 complex128 20 steps: 236 against 234 us a call), while capturing and
+  // instantiating the graphs took 250 to 600 us, on every new buffer.
   static constexpr int kGraphLevels = 6;
+  static constexpr long kGraphAtOnce = 128;
   hipStream_t cap = nullptr;
   hipGraphExec_t gexec[kGraphLevels] = {};
   void* gpsi = nullptr;
+  void* seen = nullptr;
   bool use_graph = true;
   // 3D, split 0: the graph body runs its z-local passes (X, y) per z-slab, the slabs alternating between two streams (0: off)
   int slabs = 0;
@@ -502,12 +508,11 @@ void drop_graph(sgp_ctx* c) {
   c->gpsi = nullptr;
 }
 
-// Capture the body graphs of 1, 2, 4, ..., 2^(kGraphLevels-1) steps for state psi
-// (all at once, so that a later call with another step count captures nothing).
+// The body graph of 2^k steps for state psi, captured if there is none.
 template <typename T>
-hipError_t get_graphs(sgp_ctx* c, void* psi) {
-  if (c->gpsi == psi && c->gexec[0]) return hipSuccess;
-  drop_graph(c);
+hipError_t get_graph(sgp_ctx* c, void* psi, int k) {
+  if (c->gpsi != psi) drop_graph(c);
+  if (c->gexec[k]) return hipSuccess;
   hipError_t e;
   if (!c->cap) {
     e = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking);
@@ -520,25 +525,23 @@ hipError_t get_graphs(sgp_ctx* c, void* psi) {
       if (!c->pev[i]) e = hipEventCreateWithFlags(&c->pev[i], hipEventDisableTiming);
     if (e != hipSuccess) return e;
   }
-  for (int k = 0; k < sgp_ctx::kGraphLevels; ++k) {
-    e = hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) { drop_graph(c); return e; }
-    hipError_t e1 = slabs ? enqueue_body_slabs<T>(c, c->cap, c->cap2, psi, 1 << k)
-                          : enqueue_body<T>(c, c->cap, psi, 1 << k);
-    hipGraph_t g = nullptr;
-    e = hipStreamEndCapture(c->cap, &g);
-    if (e1 != hipSuccess || e != hipSuccess) {
-      if (g) (void)hipGraphDestroy(g);
-      drop_graph(c);
-      return e1 != hipSuccess ? e1 : e;
-    }
-    e = hipGraphInstantiate(&c->gexec[k], g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) { c->gexec[k] = nullptr; drop_graph(c); return e; }
-    // stage the executable graph on the device now, not at its first replay
-    e = hipGraphUpload(c->gexec[k], c->st);
-    if (e != hipSuccess) { drop_graph(c); return e; }
+  e = hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal);
+  if (e != hipSuccess) { drop_graph(c); return e; }
+  hipError_t e1 = slabs ? enqueue_body_slabs<T>(c, c->cap, c->cap2, psi, 1 << k)
+                        : enqueue_body<T>(c, c->cap, psi, 1 << k);
+  hipGraph_t g = nullptr;
+  e = hipStreamEndCapture(c->cap, &g);
+  if (e1 != hipSuccess || e != hipSuccess) {
+    if (g) (void)hipGraphDestroy(g);
+    drop_graph(c);
+    return e1 != hipSuccess ? e1 : e;
   }
+  e = hipGraphInstantiate(&c->gexec[k], g, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(g);
+  if (e != hipSuccess) { c->gexec[k] = nullptr; drop_graph(c); return e; }
+  // stage the executable graph on the device now, not at its first replay
+  e = hipGraphUpload(c->gexec[k], c->st);
+  if (e != hipSuccess) { drop_graph(c); return e; }
   c->gpsi = psi;
   return hipSuccess;
 }
@@ -551,21 +554,22 @@ int step_impl(sgp_ctx* c, void* psi, long nsteps) {
   hipError_t e = run_xpass<T>(c, c->st, X_FIRST, psi, nl[0], CLOCK_ARG, c->t);
   if (e != hipSuccess) return hip_fail(c, e, "X-pass launch");
   long nbody = nsteps - 1;
-  if (c->use_graph && nbody > 0) {
+  const bool graph = c->use_graph && (psi == c->gpsi || psi == c->seen || nbody >= sgp_ctx::kGraphAtOnce || slab_body(c));
+  c->seen = psi;
+  if (graph && nbody > 0) {
     // the body steps replayed from graphs: nbody / 2^(L-1) replays of the largest,
     // then one replay per binary digit of the remainder (largest first)
-    e = get_graphs<T>(c, psi);
-    if (e != hipSuccess) return hip_fail(c, e, "graph capture");
     const int top = sgp_ctx::kGraphLevels - 1;
-    for (long i = 0; i < (nbody >> top); ++i) {
-      e = hipGraphLaunch(c->gexec[top], c->st);
-      if (e != hipSuccess) return hip_fail(c, e, "graph launch");
-    }
-    for (int k = top - 1; k >= 0; --k)
-      if ((nbody >> k) & 1) {
+    for (int k = top; k >= 0; --k) {
+      const long reps = k == top ? nbody >> top : (nbody >> k) & 1;
+      if (reps == 0) continue;
+      e = get_graph<T>(c, psi, k);
+      if (e != hipSuccess) return hip_fail(c, e, "graph capture");
+      for (long i = 0; i < reps; ++i) {
         e = hipGraphLaunch(c->gexec[k], c->st);
         if (e != hipSuccess) return hip_fail(c, e, "graph launch");
       }
+    }
     nbody = 0;
   }
   if (nbody > 0) {
@@ -730,6 +734,7 @@ int set_plan_impl(sgp_ctx* c, int axis, int e) {
 template <typename T>
 int autotune_impl(sgp_ctx* c, void* psi, int steps, int out_e[3], double* best_ms) {
   const double t_save = c->t;
+  c->seen = psi;  // the untimed call of a candidate captures its graphs
   hipEvent_t e0, e1;
   hipError_t r = hipEventCreate(&e0);
   if (r != hipSuccess) return hip_fail(c, r, "event create");
@@ -1511,6 +1516,7 @@ struct sgp_ensemble {
   std::vector<int> body, tail;
   std::vector<void*> psis;
   bool args_ok = false;
+  bool called = false;
   bool use_graph = true;
   bool batched = true;
   hipStream_t cap = nullptr;
@@ -1578,6 +1584,46 @@ void drop_egraph(sgp_ensemble* e) {
   if (e->gexec) (void)hipGraphExecDestroy(e->gexec);
   e->gexec = nullptr;
   e->gsteps = 0;
+}
+
+// What changes between two calls of an ensemble: the state pointers (every slot) and the
+// host clock of the first pass (slot 0, with each instance's trap angle).  Passed to a
+// kernel as arguments, kPatch instances a launch, so that a call neither copies from the
+// host nor waits for the stream.
+constexpr int kPatch = 64;
+struct ArgsPatch {
+  void* state[kPatch];
+  double trap[kPatch][2];
+};
+__global__ void k_patch_args(PassArgs* __restrict__ args, int n, int ns, int i0, int cnt, double s_arg, ArgsPatch p) {
+  const int j = threadIdx.x % kPatch, slot = threadIdx.x / kPatch;
+  if (j >= cnt) return;
+  for (int sl = slot; sl < ns; sl += blockDim.x / kPatch) args[(size_t)sl * n + i0 + j].state = p.state[j];
+  if (slot == 0) {
+    PassArgs& a = args[i0 + j];
+    a.s_arg = s_arg;
+    a.trap_c = p.trap[j][0];
+    a.trap_s = p.trap[j][1];
+  }
+}
+
+hipError_t ens_patch_args(sgp_ensemble* e) {
+  for (int i0 = 0; i0 < e->n; i0 += kPatch) {
+    ArgsPatch p;
+    const int cnt = std::min(kPatch, e->n - i0);
+    for (int j = 0; j < cnt; ++j) {
+      PassArgs a = base_args(e->ctx[i0 + j]);
+      host_clock(a, e->t);
+      p.state[j] = e->psis[i0 + j];
+      p.trap[j][0] = a.trap_c;
+      p.trap[j][1] = a.trap_s;
+    }
+    hipLaunchKernelGGL(k_patch_args, dim3(1), dim3(4 * kPatch), 0, e->st, (PassArgs*)(e->ws + e->off_args), e->n,
+                       (int)e->slots.size(), i0, cnt, e->t, p);
+    hipError_t r = hipGetLastError();
+    if (r != hipSuccess) return r;
+  }
+  return hipSuccess;
 }
 
 // Build all PassArgs slots for the current state pointers and upload them.
@@ -1735,7 +1781,10 @@ int ens_step_impl(sgp_ensemble* e, long nsteps) {
   if (r != hipSuccess) return efail(e, SGP_ERR_HIP, std::string("batched launch: ") + hipGetErrorString(r));
   long nbody = nsteps - 1;
   const int G = 16;
-  if (e->use_graph && nbody >= G) {
+  // captured from the second call on, or for a long first one (as for single grids)
+  const bool graph = e->use_graph && nbody >= G && (e->called || nbody >= sgp_ctx::kGraphAtOnce);
+  e->called = true;
+  if (graph) {
     if (!e->gexec || e->gsteps != G) {
       drop_egraph(e);
       if (!e->cap && (r = hipStreamCreateWithFlags(&e->cap, hipStreamNonBlocking)) != hipSuccess)
@@ -1997,13 +2046,11 @@ int sgp_ensemble_step(sgp_ensemble* e, void* const* psi_devs, long nsteps) {
     e->t += nsteps * e->tau;
     return SGP_OK;
   }
-  bool same = e->args_ok;
-  for (int i = 0; i < e->n && same; ++i) same = e->psis[i] == psi_devs[i];
-  // the first X-pass of a call carries the current clock: re-upload every call
+  // the first X-pass of a call carries the current clock; the captured graph reads the
+  // argument slots, so it holds for any state pointers
   e->psis.assign(psi_devs, psi_devs + e->n);
-  hipError_t r = ens_upload_args(e);
+  hipError_t r = e->args_ok ? ens_patch_args(e) : ens_upload_args(e);
   if (r != hipSuccess) return efail(e, SGP_ERR_HIP, "argument upload");
-  if (!same) drop_egraph(e);
   e->args_ok = true;
   int rc = e->dtype == SGP_C64 ? ens_step_impl<float>(e, nsteps) : ens_step_impl<double>(e, nsteps);
   if (rc == SGP_OK) e->t += nsteps * e->tau;
@@ -2049,6 +2096,7 @@ int sgp_ensemble_autotune(sgp_ensemble* e, void* const* psi_devs, int steps, dou
   if (!e->ws) return efail(e, SGP_ERR_STATE, "no workspace set");
   if (e->scheme == 0) return efail(e, SGP_ERR_STATE, "propagator not built");
   const double t_save = e->t;
+  e->called = true;  // the untimed call of a candidate captures its graph
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t r = hipEventCreate(&e0);
   if (r == hipSuccess) r = hipEventCreate(&e1);
