@@ -30,18 +30,13 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 template <int... Rs>
 std::vector<int> radix_list(RadixList<Rs...>) { return {Rs...}; }
 
-template <int N, int E>
-std::vector<int> plan_of(bool fwd) {
-  return fwd ? radix_list(typename Plan<N, E>::fwd{}) : radix_list(typename Plan<N, E>::inv{});
-}
-
 bool supported_n(int n) {
   return n == 16 || n == 32 || n == 64 || n == 128 || n == 192 || n == 256 || n == 384 || n == 512 || n == 768;
 }
 
-std::vector<int> plan_radices(int n, int e, bool fwd) {
+std::vector<int> plan_radices(int n, int e) {
 #define SGP_PLAN(NN, EE) \
-  if (n == NN && e == EE) return plan_of<NN, EE>(fwd);
+  if (n == NN && e == EE) return radix_list(typename Plan<NN, EE>::radices{});
   SGP_PLAN(16, 4) SGP_PLAN(32, 4) SGP_PLAN(64, 4) SGP_PLAN(128, 4) SGP_PLAN(256, 4) SGP_PLAN(512, 4)
   SGP_PLAN(16, 8) SGP_PLAN(32, 8) SGP_PLAN(64, 8) SGP_PLAN(128, 8) SGP_PLAN(256, 8) SGP_PLAN(512, 8)
   SGP_PLAN(64, 16) SGP_PLAN(128, 16) SGP_PLAN(256, 16) SGP_PLAN(512, 16)
@@ -88,11 +83,11 @@ struct sgp_ctx {
   char* ws = nullptr;
   size_t ws_bytes = 0;
   size_t total = 0;
-  size_t off_tw[3][2];
+  size_t off_tw[3];
   // 3D: width of the line kernel of the axis's pass (x: X kinds, y: C_PROP, z: C_KIN), 0 =
-  // none, and its twiddle tables
+  // none, and its twiddle table
   int line_e[3] = {0, 0, 0};
-  size_t off_twl[3][2];
+  size_t off_twl[3];
   size_t off_cs[4];      // (C - 1, S) table per distinct linear substep length
   size_t off_kin[4][3];
   size_t off_clock;
@@ -181,34 +176,30 @@ struct TS4 {
   }
 };
 
-// Twiddle tables of plan width e of an axis at workspace offsets off[2].
+// Twiddle table of plan width e of an axis at a workspace offset.
 template <typename T>
-hipError_t upload_tables(sgp_ctx* c, int ax, int e, const size_t* off) {
-  for (int dir = 0; dir < 2; ++dir) {
-    auto tab = twiddle_table(plan_radices(c->g.n[ax], e, dir == 0));
-    // each twiddle as a (hi, lo) pair: hi = w rounded to T, lo = (w - hi) rounded
-    std::vector<T> buf(4 * tab.size() + 4);
-    for (size_t i = 0; i < tab.size(); ++i) {
-      T hr = (T)tab[i].real(), hi = (T)tab[i].imag();
-      buf[4 * i] = hr;
-      buf[4 * i + 1] = hi;
-      buf[4 * i + 2] = (T)(tab[i].real() - (double)hr);
-      buf[4 * i + 3] = (T)(tab[i].imag() - (double)hi);
-    }
-    if (tab.empty()) continue;
-    hipError_t r = hipMemcpyAsync(c->at(off[dir]), buf.data(), sizeof(T) * 4 * tab.size(), hipMemcpyHostToDevice, c->st);
-    if (r == hipSuccess) r = hipStreamSynchronize(c->st);
-    if (r != hipSuccess) return r;
+hipError_t upload_table(sgp_ctx* c, int ax, int e, size_t off) {
+  auto tab = twiddle_table(plan_radices(c->g.n[ax], e));
+  // each twiddle as a (hi, lo) pair: hi = w rounded to T, lo = (w - hi) rounded
+  std::vector<T> buf(4 * tab.size() + 4);
+  for (size_t i = 0; i < tab.size(); ++i) {
+    T hr = (T)tab[i].real(), hi = (T)tab[i].imag();
+    buf[4 * i] = hr;
+    buf[4 * i + 1] = hi;
+    buf[4 * i + 2] = (T)(tab[i].real() - (double)hr);
+    buf[4 * i + 3] = (T)(tab[i].imag() - (double)hi);
   }
-  return hipSuccess;
+  if (tab.empty()) return hipSuccess;
+  hipError_t r = hipMemcpyAsync(c->at(off), buf.data(), sizeof(T) * 4 * tab.size(), hipMemcpyHostToDevice, c->st);
+  return r == hipSuccess ? hipStreamSynchronize(c->st) : r;
 }
 
 template <typename T>
 hipError_t upload_twiddles(sgp_ctx* c) {
   hipError_t r = hipSuccess;
   for (int ax = 0; ax < c->g.dim && r == hipSuccess; ++ax) {
-    r = upload_tables<T>(c, ax, c->elems(ax), c->off_tw[ax]);
-    if (r == hipSuccess && c->line_e[ax]) r = upload_tables<T>(c, ax, c->line_e[ax], c->off_twl[ax]);
+    r = upload_table<T>(c, ax, c->elems(ax), c->off_tw[ax]);
+    if (r == hipSuccess && c->line_e[ax]) r = upload_table<T>(c, ax, c->line_e[ax], c->off_twl[ax]);
   }
   return r;
 }
@@ -264,8 +255,7 @@ void column_geometry(const sgp_ctx* c, int axis, PassArgs& a) {
     a.nouter = ny;
     a.outer_stride = 5L * nx;
   }
-  a.tw_fwd = c->at(c->off_tw[axis][0]);
-  a.tw_inv = c->at(c->off_tw[axis][1]);
+  a.tw = c->at(c->off_tw[axis]);
   a.nu_scale_l = kPi / c->g.L[axis];
 }
 
@@ -286,9 +276,7 @@ template <typename T>
 hipError_t launch_axis(sgp_ctx* c, int kind, int axis, void* psi, PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
   const int n = c->g.n[axis];
   const bool line = c->line_e[axis] && line_elems(kind, n, (int)c->esize, c->npts());
-  const size_t* tw = line ? c->off_twl[axis] : c->off_tw[axis];
-  a.tw_fwd = c->at(tw[0]);
-  a.tw_inv = c->at(tw[1]);
+  a.tw = c->at(line ? c->off_twl[axis] : c->off_tw[axis]);
   return line ? launch_line<T>(kind, psi, a, n, c->line_e[axis], st, ev)
               : launch_pass<T>(kind, psi, a, n, c->elems(axis), st, ev);
 }
@@ -823,8 +811,7 @@ int observables_impl(sgp_ctx* c, const void* psi, double out[12]) {
   for (int axis = 0; axis < c->g.dim; ++axis) {
     PassArgs a = base_args(c);
     if (axis == 0) {
-      a.tw_fwd = c->at(c->off_tw[0][0]);
-      a.tw_inv = c->at(c->off_tw[0][1]);
+      a.tw = c->at(c->off_tw[0]);
       a.nu_scale_l = kPi / c->g.L[0];
     } else {
       column_geometry(c, axis, a);
@@ -908,8 +895,7 @@ int jz_inner_impl(sgp_ctx* c, const void* u, const void* v, double out[2]) {
   for (int axis = 0; axis < 2; ++axis) {
     PassArgs a = base_args(c);
     if (axis == 0) {
-      a.tw_fwd = c->at(c->off_tw[0][0]);
-      a.tw_inv = c->at(c->off_tw[0][1]);
+      a.tw = c->at(c->off_tw[0]);
       a.nu_scale_l = kPi / c->g.L[0];
     } else {
       column_geometry(c, 1, a);
@@ -983,8 +969,7 @@ int observables_device_impl(sgp_ctx* c, const void* psi, double* sp, long nbmax,
   for (int axis = 0; axis < c->g.dim; ++axis) {
     PassArgs a = base_args(c);
     if (axis == 0) {
-      a.tw_fwd = c->at(c->off_tw[0][0]);
-      a.tw_inv = c->at(c->off_tw[0][1]);
+      a.tw = c->at(c->off_tw[0]);
       a.nu_scale_l = kPi / c->g.L[0];
     } else {
       column_geometry(c, axis, a);
@@ -1013,8 +998,7 @@ template <typename T>
 hipError_t run_shear(sgp_ctx* c, void* psi, int kind, double coef, bool cph, double cphase) {
   PassArgs a = base_args(c);
   if (kind == X_SHEAR) {
-    a.tw_fwd = c->at(c->off_tw[0][0]);
-    a.tw_inv = c->at(c->off_tw[0][1]);
+    a.tw = c->at(c->off_tw[0]);
   } else {
     column_geometry(c, 1, a);
   }
@@ -1164,24 +1148,22 @@ int sgp_create(const sgp_grid* grid, const sgp_params* params, int dtype, void* 
   for (int ax = 0; ax < c->g.dim; ++ax) c->plan_e[ax] = default_elems(c->g.n[ax]);
   // workspace layout
   size_t off = 0;
-  for (int ax = 0; ax < 3; ++ax)
-    for (int dir = 0; dir < 2; ++dir) {
-      c->off_tw[ax][dir] = off;
-      // room for the largest table over the plans of this axis (plans can change later)
-      size_t most = 0;
-      if (ax < c->g.dim)
-        for (int e : plan_widths(c->g.n[ax], (int)c->esize))
-          most = std::max(most, twiddle_table(plan_radices(c->g.n[ax], e, dir == 0)).size());
-      if (ax < c->g.dim) off += align256(4 * c->esize * (most + 1));
-    }
+  for (int ax = 0; ax < 3; ++ax) {
+    c->off_tw[ax] = off;
+    // room for the largest table over the plans of this axis (plans can change later)
+    size_t most = 0;
+    if (ax < c->g.dim)
+      for (int e : plan_widths(c->g.n[ax], (int)c->esize))
+        most = std::max(most, twiddle_table(plan_radices(c->g.n[ax], e)).size());
+    if (ax < c->g.dim) off += align256(4 * c->esize * (most + 1));
+  }
   if (c->g.dim == 3) {
     const int kind[3] = {X_MID, C_PROP, C_KIN};
     for (int ax = 0; ax < 3; ++ax) {
       c->line_e[ax] = line_elems(kind[ax], c->g.n[ax], (int)c->esize, c->npts());
-      for (int dir = 0; dir < 2 && c->line_e[ax]; ++dir) {
-        c->off_twl[ax][dir] = off;
-        off += align256(4 * c->esize * (twiddle_table(plan_radices(c->g.n[ax], c->line_e[ax], dir == 0)).size() + 1));
-      }
+      if (!c->line_e[ax]) continue;
+      c->off_twl[ax] = off;
+      off += align256(4 * c->esize * (twiddle_table(plan_radices(c->g.n[ax], c->line_e[ax])).size() + 1));
     }
   }
   const size_t nxy = (size_t)c->g.n[0] * c->g.n[1];
@@ -1639,8 +1621,7 @@ hipError_t ens_upload_args(sgp_ensemble* e) {
       a.gacc = (double*)c->at(c->off_gacc);
       a.d = S.d;
       if (S.kind != C_PROP) {
-        a.tw_fwd = c->at(c->off_tw[0][0]);
-        a.tw_inv = c->at(c->off_tw[0][1]);
+        a.tw = c->at(c->off_tw[0]);
         a.clock_mode = S.kind == X_FIRST ? CLOCK_ARG : CLOCK_DEVICE;
         host_clock(a, e->t);
         a.n_line = c->g.n[0];
@@ -1837,8 +1818,7 @@ PassArgs ens_xargs(sgp_ctx* c, void* state, int kind, double d, double s, void* 
   PassArgs a = base_args(c);
   a.state = state;
   a.n_line = c->g.n[0];
-  a.tw_fwd = c->at(c->off_tw[0][0]);
-  a.tw_inv = c->at(c->off_tw[0][1]);
+  a.tw = c->at(c->off_tw[0]);
   a.d = d;
   host_clock(a, s);
   a.clock_mode = kind == X_MID || kind == X_LAST ? CLOCK_DEVICE : CLOCK_ARG;

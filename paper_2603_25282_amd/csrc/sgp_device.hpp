@@ -77,6 +77,21 @@ __device__ __forceinline__ T sqrt_nn(T x) {
 }
 
 
+// Keep a value where it is computed (and its uses from being traced back to it).
+template <typename T>
+__device__ __forceinline__ cx<T> pin(cx<T> z) {
+  asm volatile("" : "+v"(z.re), "+v"(z.im));
+  return z;
+}
+__device__ __forceinline__ uint32_t pin(uint32_t i) {
+  asm volatile("" : "+v"(i));
+  return i;
+}
+__device__ __forceinline__ uint64_t pin(uint64_t i) {
+  asm volatile("" : "+v"(i));
+  return i;
+}
+
 // ---------------------------------------------------------------------------
 // Small DFT kernels, y_q = sum_s x_s exp(SIGN 2 pi i s q / R), in place.
 // ---------------------------------------------------------------------------
@@ -295,8 +310,14 @@ struct Dft<8, SIGN, T> {
 // register layout.  Twiddles come from a per-pass table: for each k in [0, NS)
 // the R-1 values w^(r k), r = 1..R-1, each stored as a (hi, lo) pair.
 //
-// LDS exchange buffers are split re / im and padded by one slot every 8 entries
-// (bank-conflict-free stride-8 writes).
+// The inverse is the transposed sequence: the same passes in reverse order, each a
+// length-R inverse DFT of the elements (j / NS) NS R + (j mod NS) + r NS followed by the
+// conjugate twiddles, landing at j + (N/R) r.  It reads the forward transform's table, so
+// a pass with both directions stages one table: at 768 points (FP32) 47 instead of 59 KiB
+// of LDS, three blocks per CU instead of two (768^2 complex64 x-pass 34.6 -> 26.8 us).
+//
+// LDS exchange buffers are padded by one slot every 8 entries (bank-conflict-free
+// stride-8 accesses).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 3); }
 template <int N> struct LdsLine { static constexpr int size = N + N / 8; };
@@ -328,7 +349,7 @@ __device__ __forceinline__ void lds_sync() {
 
 // NBUF: how many components share one LDS exchange round (1 <= NBUF <= NC); buffer
 // b of a line starts at b * lds_stride.
-template <typename T, int N, int E, int R, int NS, int SIGN, bool LAST, int NC, int NBUF, int SYNC>
+template <typename T, int N, int E, int R, int NS, bool LAST, int NC, int NBUF, int SYNC>
 __device__ __forceinline__ void fft_pass(cx<T> (&v)[NC][E], cx<T>* __restrict__ lx, int t,
                                          const cx<T>* __restrict__ tw, int lds_stride) {
   constexpr int TL = N / E;
@@ -345,10 +366,8 @@ __device__ __forceinline__ void fft_pass(cx<T> (&v)[NC][E], cx<T>* __restrict__ 
 #pragma unroll
       for (int r = 1; r < R; ++r) {
         // table order [r - 1][k]: adjacent lanes (adjacent k) read adjacent entries
-        cx<T> z = tw[2 * ((r - 1) * NS + k)];
-        cx<T> zl = tw[2 * ((r - 1) * NS + k) + 1];
-        w[b][r - 1] = SIGN < 0 ? z : conj(z);
-        wl[b][r - 1] = SIGN < 0 ? zl : conj(zl);
+        w[b][r - 1] = tw[2 * ((r - 1) * NS + k)];
+        wl[b][r - 1] = tw[2 * ((r - 1) * NS + k) + 1];
       }
     }
   }
@@ -363,7 +382,7 @@ __device__ __forceinline__ void fft_pass(cx<T> (&v)[NC][E], cx<T>* __restrict__ 
 #pragma unroll
         for (int r = 1; r < R; ++r) x[r] = twmul(x[r], w[b][r - 1], wl[b][r - 1]);
       }
-      Dft<R, SIGN, T>::run(x);
+      Dft<R, -1, T>::run(x);
       if constexpr (LAST) {
 #pragma unroll
         for (int r = 0; r < R; ++r) v[c][b + B * r] = x[r];
@@ -394,109 +413,188 @@ __device__ __forceinline__ void fft_pass(cx<T> (&v)[NC][E], cx<T>* __restrict__ 
   }
 }
 
-// Radix plans.  Forward passes run in the listed order, the inverse runs the
-// reverse order so that the two share the register layout at both ends.
+// Inverse pass (see above).  FIRST: the transform's first inverse pass (the forward's last),
+// whose inputs are this thread's registers; the others read them through LDS.
+template <typename T, int N, int E, int R, int NS, bool FIRST, int NC, int NBUF, int SYNC>
+__device__ __forceinline__ void fft_pass_inv(cx<T> (&v)[NC][E], cx<T>* __restrict__ lx, int t,
+                                             const cx<T>* __restrict__ tw, int lds_stride) {
+  constexpr int TL = N / E;
+  constexpr int B = E / R;
+  static_assert(E % R == 0, "radix must divide the elements per thread");
+  auto exchange = [&](int c0) {
+#pragma unroll
+    for (int c = c0; c < c0 + NBUF && c < NC; ++c)
+#pragma unroll
+      for (int m = 0; m < E; ++m) lx[lds_pad(t + TL * m) + (c % NBUF) * lds_stride] = v[c][m];
+    lds_sync<SYNC>();
+#pragma unroll
+    for (int c = c0; c < c0 + NBUF && c < NC; ++c)
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int j = t + TL * b;
+        const int base = (j / NS) * NS * R + (j % NS);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[c][b + B * r] = lx[lds_pad(base + r * NS) + (c % NBUF) * lds_stride];
+      }
+    lds_sync<SYNC>();
+  };
+  if constexpr (!FIRST) exchange(0);
+  cx<T> w[B][R > 1 ? R - 1 : 1], wl[B][R > 1 ? R - 1 : 1];
+  if constexpr (NS > 1) {
+    // an index of its own: seen to be the forward pass's entries, the twiddles stay in
+    // registers from there to here (26 more in the 128-point z-pass, 33.7 -> 38.6 us)
+    const int tk = (int)pin((uint32_t)t);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int k = (tk + TL * b) % NS;
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        w[b][r - 1] = conj(tw[2 * ((r - 1) * NS + k)]);
+        wl[b][r - 1] = conj(tw[2 * ((r - 1) * NS + k) + 1]);
+      }
+    }
+  }
+  // the next components' exchange is issued ahead of a component's butterflies
+#pragma unroll
+  for (int c0 = 0; c0 < NC; c0 += NBUF) {
+    if constexpr (!FIRST)
+      if (c0 + NBUF < NC) exchange(c0 + NBUF);
+#pragma unroll
+    for (int c = c0; c < c0 + NBUF && c < NC; ++c)
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        cx<T> x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = v[c][b + B * r];
+        Dft<R, +1, T>::run(x);
+        v[c][b] = x[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[c][b + B * r] = NS > 1 ? twmul(x[r], w[b][r - 1], wl[b][r - 1]) : x[r];
+      }
+  }
+}
+
+// Radix plans, in the order of the forward passes: the smallest radix last, where it saves
+// the most twiddles (the first pass has none; 128 = 8.8.2 multiplies 11/8 of its elements,
+// 2.8.8 14/8) and the first exchange has radix-8 stride (9 with the padding, free of bank
+// conflicts in both directions).
 template <int... Rs> struct RadixList {};
 template <int N, int E> struct Plan;
 // E = 8 (defaults for powers of two)
-template <> struct Plan<16, 8> { using fwd = RadixList<2, 8>; using inv = RadixList<8, 2>; };
-template <> struct Plan<32, 8> { using fwd = RadixList<4, 8>; using inv = RadixList<8, 4>; };
-template <> struct Plan<64, 8> { using fwd = RadixList<8, 8>; using inv = RadixList<8, 8>; };
-template <> struct Plan<128, 8> { using fwd = RadixList<2, 8, 8>; using inv = RadixList<8, 8, 2>; };
-template <> struct Plan<256, 8> { using fwd = RadixList<4, 8, 8>; using inv = RadixList<8, 8, 4>; };
-template <> struct Plan<512, 8> { using fwd = RadixList<8, 8, 8>; using inv = RadixList<8, 8, 8>; };
+template <> struct Plan<16, 8> { using radices = RadixList<8, 2>; };
+template <> struct Plan<32, 8> { using radices = RadixList<8, 4>; };
+template <> struct Plan<64, 8> { using radices = RadixList<8, 8>; };
+template <> struct Plan<128, 8> { using radices = RadixList<8, 8, 2>; };
+template <> struct Plan<256, 8> { using radices = RadixList<8, 8, 4>; };
+template <> struct Plan<512, 8> { using radices = RadixList<8, 8, 8>; };
 // E = 4: radix 2 and 4 only, twice the threads per line
-template <> struct Plan<16, 4> { using fwd = RadixList<4, 4>; using inv = RadixList<4, 4>; };
-template <> struct Plan<32, 4> { using fwd = RadixList<2, 4, 4>; using inv = RadixList<4, 4, 2>; };
-template <> struct Plan<64, 4> { using fwd = RadixList<4, 4, 4>; using inv = RadixList<4, 4, 4>; };
-template <> struct Plan<128, 4> { using fwd = RadixList<2, 4, 4, 4>; using inv = RadixList<4, 4, 4, 2>; };
-template <> struct Plan<256, 4> { using fwd = RadixList<4, 4, 4, 4>; using inv = RadixList<4, 4, 4, 4>; };
-template <> struct Plan<512, 4> { using fwd = RadixList<2, 4, 4, 4, 4>; using inv = RadixList<4, 4, 4, 4, 2>; };
+template <> struct Plan<16, 4> { using radices = RadixList<4, 4>; };
+template <> struct Plan<32, 4> { using radices = RadixList<4, 4, 2>; };
+template <> struct Plan<64, 4> { using radices = RadixList<4, 4, 4>; };
+template <> struct Plan<128, 4> { using radices = RadixList<4, 4, 4, 2>; };
+template <> struct Plan<256, 4> { using radices = RadixList<4, 4, 4, 4>; };
+template <> struct Plan<512, 4> { using radices = RadixList<4, 4, 4, 4, 2>; };
 // E = 16: radix 16 for 128 (8.16) and 256 (16.16); for 64 and 512 the E = 8
 // radices, two butterflies per thread and pass
-template <> struct Plan<64, 16> { using fwd = RadixList<8, 8>; using inv = RadixList<8, 8>; };
-template <> struct Plan<128, 16> { using fwd = RadixList<8, 16>; using inv = RadixList<16, 8>; };
-template <> struct Plan<256, 16> { using fwd = RadixList<16, 16>; using inv = RadixList<16, 16>; };
-template <> struct Plan<512, 16> { using fwd = RadixList<8, 8, 8>; using inv = RadixList<8, 8, 8>; };
+template <> struct Plan<64, 16> { using radices = RadixList<8, 8>; };
+template <> struct Plan<128, 16> { using radices = RadixList<16, 8>; };
+template <> struct Plan<256, 16> { using radices = RadixList<16, 16>; };
+template <> struct Plan<512, 16> { using radices = RadixList<8, 8, 8>; };
 // 384 = 3 * 2^7: E = 12 (default) and E = 24
-template <> struct Plan<384, 12> { using fwd = RadixList<6, 4, 4, 4>; using inv = RadixList<4, 4, 4, 6>; };
-template <> struct Plan<384, 24> { using fwd = RadixList<6, 8, 8>; using inv = RadixList<8, 8, 6>; };
+template <> struct Plan<384, 12> { using radices = RadixList<6, 4, 4, 4>; };
+template <> struct Plan<384, 24> { using radices = RadixList<6, 8, 8>; };
 // 192 = 3 * 2^6 and 768 = 3 * 2^8: E = 12 (default) and E = 24 (radix 12: 4 x 3)
-template <> struct Plan<192, 12> { using fwd = RadixList<12, 4, 4>; using inv = RadixList<4, 4, 12>; };
-template <> struct Plan<192, 24> { using fwd = RadixList<3, 8, 8>; using inv = RadixList<8, 8, 3>; };
-template <> struct Plan<768, 12> { using fwd = RadixList<12, 4, 4, 4>; using inv = RadixList<4, 4, 4, 12>; };
-template <> struct Plan<768, 24> { using fwd = RadixList<12, 8, 8>; using inv = RadixList<8, 8, 12>; };
+template <> struct Plan<192, 12> { using radices = RadixList<12, 4, 4>; };
+template <> struct Plan<192, 24> { using radices = RadixList<3, 8, 8>; };
+template <> struct Plan<768, 12> { using radices = RadixList<12, 4, 4, 4>; };
+template <> struct Plan<768, 24> { using radices = RadixList<12, 8, 8>; };
 
-// Twiddle-table entries of a plan direction: NS (R - 1) per pass with NS > 1 (each
-// entry is a (hi, lo) pair of cx<T>).
+// Twiddle-table entries of a plan: NS (R - 1) per pass with NS > 1 (each entry is a
+// (hi, lo) pair of cx<T>).
 template <int... Rs>
 constexpr int tw_entries(RadixList<Rs...>) {
   int ns = 1, n = 0;
   ((n += (ns > 1 ? ns * (Rs - 1) : 0), ns *= Rs), ...);
   return n;
 }
-template <int... Rs>
-constexpr int n_passes(RadixList<Rs...>) { return (int)sizeof...(Rs); }
 template <int N, int E>
 struct TwSize {
-  static constexpr int fwd = tw_entries(typename Plan<N, E>::fwd{});
-  static constexpr int inv = tw_entries(typename Plan<N, E>::inv{});
-  // the first pass has no twiddles and ends with an exchange (a block barrier), so
-  // tables staged in LDS before the transform are visible when first read
-  static_assert(n_passes(typename Plan<N, E>::fwd{}) >= 2, "plans have at least two passes");
+  static constexpr int entries = tw_entries(typename Plan<N, E>::radices{});
 };
 
-// Copy NCX cx<T> values (a whole twiddle table) from global memory to LDS with the
-// NT threads of a block, in 16-byte pieces: rounds of up to four pieces per thread,
-// all loads of a round issued before its stores (named registers, not an array, so
-// that nothing lands in scratch memory).
-template <int NT, int NCH, int B>
-__device__ __forceinline__ void stage_round(const uint4* __restrict__ s, uint4* __restrict__ d, int tid) {
-  uint4 t0 = {}, t1 = {}, t2 = {}, t3 = {};
-  if (B + tid < NCH) t0 = s[B + tid];
-  if (NCH > B + NT && B + tid + NT < NCH) t1 = s[B + tid + NT];
-  if (NCH > B + 2 * NT && B + tid + 2 * NT < NCH) t2 = s[B + tid + 2 * NT];
-  if (NCH > B + 3 * NT && B + tid + 3 * NT < NCH) t3 = s[B + tid + 3 * NT];
-  if (B + tid < NCH) d[B + tid] = t0;
-  if (NCH > B + NT && B + tid + NT < NCH) d[B + tid + NT] = t1;
-  if (NCH > B + 2 * NT && B + tid + 2 * NT < NCH) d[B + tid + 2 * NT] = t2;
-  if (NCH > B + 3 * NT && B + tid + 3 * NT < NCH) d[B + tid + 3 * NT] = t3;
-  if constexpr (NCH > B + 4 * NT) stage_round<NT, NCH, B + 4 * NT>(s, d, tid);
-}
-
+// Copy a twiddle table (NCX cx<T> values) from global memory to LDS with the NT threads of
+// a block, in 16-byte pieces.  load() issues the first four pieces per thread (unguarded,
+// so that the state loads behind it are issued at once), store() writes them and copies
+// what is left.  Issued before the state loads, the table is in LDS, and the barrier in
+// front of an inverse transform passed, while those are in flight.
 template <typename T, int NT, int NCX>
-__device__ __forceinline__ void stage_tw(cx<T>* __restrict__ dst, const void* __restrict__ src, int tid) {
-  constexpr int NCH = NCX * (int)sizeof(cx<T>) / 16;
+struct TwStage {
+  static constexpr int NCH = NCX * (int)sizeof(cx<T>) / 16;
   static_assert(NCX * sizeof(cx<T>) % 16 == 0, "tables are whole 16-byte pieces");
-  stage_round<NT, NCH, 0>(reinterpret_cast<const uint4*>(src), reinterpret_cast<uint4*>(dst), tid);
-}
+  static constexpr int R = (NCH + NT - 1) / NT < 4 ? (NCH + NT - 1) / NT : 4;
+  // plain vectors with names of their own: uint4, or an array, lands in scratch memory in
+  // the batched kernels
+  using V = uint32_t __attribute__((ext_vector_type(4)));
+  V r0, r1, r2, r3;
+  template <int I>
+  static __device__ __forceinline__ bool in(int tid) {
+    return (I + 1) * NT <= NCH || tid + I * NT < NCH;
+  }
+  __device__ __forceinline__ void load(const void* __restrict__ src, int tid) {
+    const V* s = reinterpret_cast<const V*>(src);
+    r0 = s[in<0>(tid) ? tid : 0];
+    if constexpr (R > 1) r1 = s[in<1>(tid) ? tid + NT : 0];
+    if constexpr (R > 2) r2 = s[in<2>(tid) ? tid + 2 * NT : 0];
+    if constexpr (R > 3) r3 = s[in<3>(tid) ? tid + 3 * NT : 0];
+  }
+  __device__ __forceinline__ void store(cx<T>* __restrict__ dst, const void* __restrict__ src, int tid) {
+    V* d = reinterpret_cast<V*>(dst);
+    if (in<0>(tid)) d[tid] = r0;
+    if constexpr (R > 1)
+      if (in<1>(tid)) d[tid + NT] = r1;
+    if constexpr (R > 2)
+      if (in<2>(tid)) d[tid + 2 * NT] = r2;
+    if constexpr (R > 3)
+      if (in<3>(tid)) d[tid + 3 * NT] = r3;
+    if constexpr (NCH > R * NT)
+      for (int k = tid + R * NT; k < NCH; k += NT) d[k] = reinterpret_cast<const V*>(src)[k];
+  }
+};
 
-template <typename T, int N, int E, int SIGN, int NS, int NC, int NBUF, int SYNC, int R, int... Rest>
+template <typename T, int N, int E, int NS, int NC, int NBUF, int SYNC, int R, int... Rest>
 __device__ __forceinline__ void fft_passes(cx<T> (&v)[NC][E], cx<T>* lx, int t, const cx<T>* tw,
                                            int lds_stride) {
   constexpr bool last = sizeof...(Rest) == 0;
-  fft_pass<T, N, E, R, NS, SIGN, last, NC, NBUF, SYNC>(v, lx, t, tw, lds_stride);
-  if constexpr (!last) {
-    fft_passes<T, N, E, SIGN, NS * R, NC, NBUF, SYNC, Rest...>(v, lx, t,
-                                                              tw + (NS > 1 ? 2 * NS * (R - 1) : 0), lds_stride);
-  }
+  fft_pass<T, N, E, R, NS, last, NC, NBUF, SYNC>(v, lx, t, tw, lds_stride);
+  if constexpr (!last)
+    fft_passes<T, N, E, NS * R, NC, NBUF, SYNC, Rest...>(v, lx, t, tw + (NS > 1 ? 2 * NS * (R - 1) : 0), lds_stride);
+}
+
+template <typename T, int N, int E, int NS, int NC, int NBUF, int SYNC, int R, int... Rest>
+__device__ __forceinline__ void fft_passes_inv(cx<T> (&v)[NC][E], cx<T>* lx, int t, const cx<T>* tw,
+                                               int lds_stride) {
+  constexpr bool first = sizeof...(Rest) == 0;  // the forward's last pass runs first
+  if constexpr (!first)
+    fft_passes_inv<T, N, E, NS * R, NC, NBUF, SYNC, Rest...>(v, lx, t, tw + (NS > 1 ? 2 * NS * (R - 1) : 0),
+                                                            lds_stride);
+  fft_pass_inv<T, N, E, R, NS, first, NC, NBUF, SYNC>(v, lx, t, tw, lds_stride);
 }
 
 template <typename T, int N, int E, int SIGN, int NC, int NBUF, int SYNC, int... Rs>
 __device__ __forceinline__ void fft_run(RadixList<Rs...>, cx<T> (&v)[NC][E], cx<T>* lx, int t,
                                         const cx<T>* tw, int lds_stride) {
-  fft_passes<T, N, E, SIGN, 1, NC, NBUF, SYNC, Rs...>(v, lx, t, tw, lds_stride);
+  if constexpr (SIGN < 0) fft_passes<T, N, E, 1, NC, NBUF, SYNC, Rs...>(v, lx, t, tw, lds_stride);
+  else fft_passes_inv<T, N, E, 1, NC, NBUF, SYNC, Rs...>(v, lx, t, tw, lds_stride);
 }
 
-// Forward (SIGN = -1) or inverse (SIGN = +1) unscaled transform of NC components.
-// tw points at the table of the plan for this direction.
+// Forward (SIGN = -1) or inverse (SIGN = +1) unscaled transform of NC components with the
+// plan's table.  A table staged in LDS must be visible (a barrier) before an inverse
+// transform, whose first pass reads it; a forward transform's first pass does not and ends
+// with an exchange.
 template <typename T, int N, int E, int SIGN, int NC, int NBUF, int SYNC>
 __device__ __forceinline__ void fft_line(cx<T> (&v)[NC][E], cx<T>* lx, int t, const cx<T>* tw,
                                          int lds_stride) {
-  if constexpr (SIGN < 0)
-    fft_run<T, N, E, SIGN, NC, NBUF, SYNC>(typename Plan<N, E>::fwd{}, v, lx, t, tw, lds_stride);
-  else
-    fft_run<T, N, E, SIGN, NC, NBUF, SYNC>(typename Plan<N, E>::inv{}, v, lx, t, tw, lds_stride);
+  fft_run<T, N, E, SIGN, NC, NBUF, SYNC>(typename Plan<N, E>::radices{}, v, lx, t, tw, lds_stride);
 }
 
 // ---------------------------------------------------------------------------

@@ -36,9 +36,7 @@ struct PassArgs {
   long outer_stride;     // elements between outer slabs
   int dim;
   int n_q;               // points along y (the q axis of the propagator)
-  // FFT twiddles of the line's axis
-  const void* tw_fwd;
-  const void* tw_inv;
+  const void* tw;        // FFT twiddles of the line's axis
   // propagator
   const void* cs;        // (C - 1, S) per (q, p)
   const void* kin_a;     // exp(-i d nu^2/2) - 1 along x

@@ -20,19 +20,10 @@ namespace sgp {
 // at 128^3; eight: 58.8.
 constexpr int kLineWaves = 4;
 
-// Keep a value where it is computed: without it the compiler sinks the pointwise maps of
-// all E points past each other's branches to the transform behind them and holds their
-// coefficients in 100 more registers.
-template <typename T>
-__device__ __forceinline__ cx<T> pin(cx<T> z) {
-  asm volatile("" : "+v"(z.re), "+v"(z.im));
-  return z;
-}
-
-__device__ __forceinline__ uint32_t pin(uint32_t i) {
-  asm volatile("" : "+v"(i));
-  return i;
-}
+// Wavefronts per SIMD to keep room for: 80 registers of state come out at 150 to 175 in
+// all, and above 168 (two wavefronts) the 192x128x64 complex128 y-pass takes 70 instead of
+// 58 us, the 256^3 complex64 z-pass 361 instead of 318.  (Four, 128 registers, spill.)
+constexpr int line_min_waves(int e, int esize) { return e * (esize / 4) == 8 ? 3 : 1; }
 
 // LDS of a wavefront: its 64/TL lines' exchanges, one component at a time, or 64 points
 // between memory order and point order.
@@ -55,15 +46,14 @@ __device__ __forceinline__ void line_reorder(cx<T> (&v)[5][E], int m, cx<T>* lx,
 }
 
 template <typename T, int N, int E, int KIND>
-__global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ psi, PassArgs a) {
+__global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T))) void k_line(cx<T>* __restrict__ psi, PassArgs a) {
   constexpr int TL = N / E;
   constexpr int W = 64 / TL;  // lines per wavefront
   constexpr int LS = PadLine<N>::size;
   constexpr bool XL = KindInfo<KIND>::XL;
-  constexpr int TWF = KindInfo<KIND>::HF ? 2 * TwSize<N, E>::fwd : 0;
-  constexpr int TWI = KindInfo<KIND>::HI ? 2 * TwSize<N, E>::inv : 0;
+  constexpr int TW = pass_tw<N, E, KIND>();
   __shared__ cx<T> xch[kLineWaves][line_lds<N, E>()];
-  __shared__ uint4 ltwr[((TWF + TWI) * (int)sizeof(cx<T>) + 15) / 16];
+  __shared__ uint4 ltwr[(TW * (int)sizeof(cx<T>) + 15) / 16];
   cx<T>* ltw = reinterpret_cast<cx<T>*>(ltwr);
 
   long nb = gridDim.x;
@@ -102,6 +92,8 @@ __global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ ps
     off[i] = (uint32_t)(((long)(e / RL) * pitch + e % RL) * (int)sizeof(cx<T>));
   }
   cx<T>* lx0 = xch[wave];
+  TwStage<T, 64 * kLineWaves, TW> stage;
+  stage.load(a.tw, threadIdx.x);
   cx<T> v[5][E];
 #pragma unroll
   for (int m = 0; m < E; ++m) {
@@ -109,10 +101,8 @@ __global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ ps
 #pragma unroll
     for (int i = 0; i < 5; ++i) v[i][m] = *reinterpret_cast<const cx<T>*>(src + off[i]);
   }
-  if constexpr (TWF > 0) stage_tw<T, 64 * kLineWaves, TWF>(ltw, a.tw_fwd, threadIdx.x);
-  if constexpr (TWI > 0) stage_tw<T, 64 * kLineWaves, TWI>(ltw + TWF, a.tw_inv, threadIdx.x);
-  const cx<T>* twf = ltw;
-  const cx<T>* twi = ltw + TWF;
+  stage.store(ltw, a.tw, threadIdx.x);
+  const cx<T>* tw = ltw;
   double ct = 1.0, st = 0.0;
   if constexpr (XL) trap_angle(a, ct, st);
   __syncthreads();
@@ -121,8 +111,8 @@ __global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ ps
 #pragma unroll
   for (int m = 0; m < E; ++m) line_reorder<T, E, true>(v, m, lx0, lane);
   cx<T>* lx = lx0 + col * LS;
-  if constexpr (KIND == X_MID || KIND == X_LAST) fft_line<T, N, E, +1, 5, 1, 1>(v, lx, t, twi, 0);
-  if constexpr (!XL) fft_line<T, N, E, -1, 5, 1, 1>(v, lx, t, twf, 0);
+  if constexpr (KIND == X_MID || KIND == X_LAST) fft_line<T, N, E, +1, 5, 1, 1>(v, lx, t, tw, 0);
+  if constexpr (!XL) fft_line<T, N, E, -1, 5, 1, 1>(v, lx, t, tw, 0);
 
   if constexpr (KIND != C_KIN) {
     if (a.store != nullptr) {
@@ -152,6 +142,8 @@ __global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ ps
 #pragma unroll
       for (int c = 0; c < 5; ++c) p[c] = v[c][m];
       nl_point<T>(p, V, K);
+      // pinned: else the compiler sinks the maps of all E points past each other's branches
+      // to the transform behind them and holds their coefficients in 100 more registers
 #pragma unroll
       for (int c = 0; c < 5; ++c) v[c][m] = pin(p[c]);
     }
@@ -191,8 +183,8 @@ __global__ __launch_bounds__(64 * kLineWaves) void k_line(cx<T>* __restrict__ ps
     }
   }
 
-  if constexpr (KIND == X_FIRST || KIND == X_MID) fft_line<T, N, E, -1, 5, 1, 1>(v, lx, t, twf, 0);
-  if constexpr (!XL) fft_line<T, N, E, +1, 5, 1, 1>(v, lx, t, twi, 0);
+  if constexpr (KIND == X_FIRST || KIND == X_MID) fft_line<T, N, E, -1, 5, 1, 1>(v, lx, t, tw, 0);
+  if constexpr (!XL) fft_line<T, N, E, +1, 5, 1, 1>(v, lx, t, tw, 0);
 
   // the offsets are made opaque here: seen through, they become 64-bit addresses of every
   // value that live through the pointwise stage (2 * 5 * E registers)

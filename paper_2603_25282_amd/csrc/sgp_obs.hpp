@@ -69,7 +69,7 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_obs(const cx<T>* __restrict
   }
   cx<T>* xl = lx + (col * 5 + c) * LS;
   // derivative along the line: FFT, multiply by i nu / N, inverse FFT
-  fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, reinterpret_cast<const cx<T>*>(a.tw_fwd), 0);
+  fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, reinterpret_cast<const cx<T>*>(a.tw), 0);
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     const int k = t + TL * m;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_obs(const cx<T>* __restrict
     const T nu = T(p * a.nu_scale_l / N);
     v[0][m] = mk<T>(-nu * v[0][m].im, nu * v[0][m].re);
   }
-  fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, reinterpret_cast<const cx<T>*>(a.tw_inv), 0);
+  fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, reinterpret_cast<const cx<T>*>(a.tw), 0);
   // tile: psi at [0, W N 5), derivative at [W N 5, 2 W N 5)
 #pragma unroll
   for (int m = 0; m < E; ++m) {

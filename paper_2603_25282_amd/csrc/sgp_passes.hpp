@@ -27,6 +27,8 @@
 // (components innermost), every thread updates whole points from the tile, and
 // the FFT threads read their elements back.
 #pragma once
+#include <type_traits>
+
 #include "sgp_device.hpp"
 #include "sgp_kernels.hpp"
 
@@ -131,10 +133,10 @@ template <int KIND> struct KindInfo {
                              KIND == C_PROP || KIND == C_ADJ || SHEAR || KIND == X_INV || KIND == C_KIN;
 };
 
-// LDS cx<T> values of the staged twiddle tables of a pass (forward table first).
+// LDS cx<T> values of the staged twiddle table of a pass.
 template <int N, int E, int KIND>
 constexpr int pass_tw() {
-  return (KindInfo<KIND>::HF ? 2 * TwSize<N, E>::fwd : 0) + (KindInfo<KIND>::HI ? 2 * TwSize<N, E>::inv : 0);
+  return KindInfo<KIND>::HF || KindInfo<KIND>::HI ? 2 * TwSize<N, E>::entries : 0;
 }
 
 // LDS elements (per re / im array) a pass needs.
@@ -165,46 +167,47 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   const int col = XL ? rest / TL : rest % W;
   const int t = XL ? rest % TL : rest / W;
 
-  // line geometry, in 32-bit element offsets (every supported state, up to
-  // 512^3 points x 5 components, has fewer than 2^31 elements)
-  int base;         // element offset of the line's first point (component 0)
-  int estride;      // element stride between consecutive points of the line
+  // Line geometry: the tile's first value (uniform, in scalar registers), the thread's byte
+  // offset from it and the element stride of the line.  The offset is 32 bits wide where a
+  // line's TL threads span less than 2^32 bytes (TL <= 64; every supported state has fewer
+  // than 2^31 elements).
+  using Off = std::conditional_t<TL <= 64, uint32_t, uint64_t>;
+  const int estride = XL ? 5 : (int)a.stride;
   int line0 = 0;    // x-lines: first line of the block (line = z * ny + y)
   int o = 0, kx0 = 0;
-  // one line per block: no idle lines, and the loads need no guard (with more lines per
-  // block the guards keep the compiler from holding all addresses at once: without them
-  // the 256^3 x-pass took 571 instead of 465 us)
-  constexpr bool FULL = W == 1;
+  cx<T>* tb;
   bool active;
+  // every supported length is a multiple of 16, so only wider tiles have idle lines
+  constexpr bool FULL = W <= 16;
   if constexpr (XL) {
     line0 = (int)tile * W;
-    const int line = line0 + col;
-    active = FULL || line < a.nlines;
-    base = (active ? line : 0) * N * 5;
-    estride = 5;
+    active = FULL || line0 + col < a.nlines;
+    tb = psi + (long)line0 * N * 5;
   } else {
     const int ncolblk = ((int)a.ncols + W - 1) / W;
     o = (int)tile / ncolblk;
     kx0 = ((int)tile % ncolblk) * W;
-    const int kx = kx0 + col;
-    active = FULL || kx < a.ncols;
-    base = o * (int)a.outer_stride + (active ? kx : 0) * 5;
-    estride = (int)a.stride;
+    active = FULL || kx0 + col < a.ncols;
+    tb = psi + (long)o * a.outer_stride + kx0 * 5;
   }
+  const Off voff = active ? ((Off)(XL ? col * N * 5 : col * 5) + (Off)t * (Off)estride + c) * (Off)sizeof(cx<T>) : 0;
 
+  constexpr int TW = pass_tw<N, E, KIND>();
+  TwStage<T, NT, (TW > 0 ? TW : 2)> stage;
+  // table first, so that the barrier behind it passes while the state is in flight; 512
+  // complex64 points measured the other way round (x-pass 14.3 against 13.9 us)
+  constexpr bool TWFIRST = sizeof(T) == 8 || E == 12;
+  if constexpr (TW > 0 && TWFIRST) stage.load(a.tw, tid);
   cx<T> v[1][E];
 #pragma unroll
   for (int m = 0; m < E; ++m)
-    v[0][m] = active ? psi[base + (t + TL * m) * estride + c] : mk<T>(T(0), T(0));
+    v[0][m] = active ? *reinterpret_cast<const cx<T>*>(reinterpret_cast<const char*>(tb + (long)(TL * m) * estride) + voff)
+                     : mk<T>(T(0), T(0));
 
   cx<T>* xl = lx + (col * 5 + c) * LS;
-  // twiddle tables staged in LDS while the state loads are in flight
-  constexpr int TWF = KindInfo<KIND>::HF ? 2 * TwSize<N, E>::fwd : 0;
-  constexpr int TWI = KindInfo<KIND>::HI ? 2 * TwSize<N, E>::inv : 0;
-  const cx<T>* twf = ltw;
-  const cx<T>* twi = ltw + TWF;
-  if constexpr (TWF > 0) stage_tw<T, NT, TWF>(ltw, a.tw_fwd, tid);
-  if constexpr (TWI > 0) stage_tw<T, NT, TWI>(ltw + TWF, a.tw_inv, tid);
+  const cx<T>* tw = ltw;
+  if constexpr (TW > 0 && !TWFIRST) stage.load(a.tw, tid);
+  if constexpr (TW > 0) stage.store(ltw, a.tw, tid);
 
   // read here, with the state loads: at its place of use, behind the transform and its
   // barriers, the clock is a round trip to memory of its own in every block
@@ -234,10 +237,12 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
     }
   }
 
-  if constexpr (KIND == X_MID || KIND == X_LAST || KIND == XA_FIRST || KIND == XA_MID || KIND == X_INV)
-    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
+  if constexpr (KIND == X_MID || KIND == X_LAST || KIND == XA_FIRST || KIND == XA_MID || KIND == X_INV) {
+    __syncthreads();  // the table
+    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
+  }
   if constexpr (KIND == C_PROP || KIND == C_ADJ || KIND == X_FWD || KindInfo<KIND>::SHEAR || KIND == C_KIN)
-    fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, twf, 0);
+    fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, tw, 0);
 
   if constexpr (KIND == C_KIN) {
     // the kinetic phase along the line, per component: coefficient k times
@@ -249,7 +254,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const cx<T> ph = kin_l[t + TL * m];
       v[0][m] = inc_apply(mk<T>(ph.re, sg * ph.im), v[0][m]);
     }
-    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
+    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
   }
 
   if constexpr (KindInfo<KIND>::SHEAR) {
@@ -276,15 +281,17 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const T vr = v[0][m].re, vi = v[0][m].im;
       v[0][m] = mk<T>(T(zr) * vr - T(zi) * vi, T(zr) * vi + T(zi) * vr);
     }
-    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
+    fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
   }
 
   // forward store mode: keep the pointwise-stage input for the adjoint
   if constexpr (PW && !ADJ) {
     if (a.store != nullptr && active) {
-      cx<T>* st = reinterpret_cast<cx<T>*>(a.store);
+      cx<T>* st = reinterpret_cast<cx<T>*>(a.store) + (tb - psi);
+      const Off so = pin(voff);
 #pragma unroll
-      for (int m = 0; m < E; ++m) st[base + (t + TL * m) * estride + c] = v[0][m];
+      for (int m = 0; m < E; ++m)
+        *reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(st + (long)(TL * m) * estride) + so) = v[0][m];
     }
   }
   double gacc[NGRAD] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -444,8 +451,8 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   }
 
   if constexpr (KIND == X_FIRST || KIND == X_MID || KIND == XA_MID || KIND == XA_LAST)
-    fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, twf, 0);
-  if constexpr (KIND == C_PROP || KIND == C_ADJ) fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, twi, 0);
+    fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, tw, 0);
+  if constexpr (KIND == C_PROP || KIND == C_ADJ) fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
 
   if constexpr (ADJ) {
     // parameter partials: block reduction in a fixed order into this block's slot
@@ -465,8 +472,11 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   }
 
   if (active) {
+    // made opaque: else the addresses of the loads stay in registers (two per value)
+    const Off so = pin(voff);
 #pragma unroll
-    for (int m = 0; m < E; ++m) psi[base + (t + TL * m) * estride + c] = v[0][m];
+    for (int m = 0; m < E; ++m)
+      *reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(tb + (long)(TL * m) * estride) + so) = v[0][m];
   }
   if constexpr (XL && !ADJ && PW) {
     if (a.clock_mode == CLOCK_ARG && tile == 0 && tid == 0) {
