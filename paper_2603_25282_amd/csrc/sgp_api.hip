@@ -94,7 +94,7 @@ struct sgp_ctx {
   size_t off_part;
   size_t off_red;        // on-device sums of the observables' block partials (3 x NOBS)
   size_t off_gacc;
-  long ngacc = 0;  // blocks with a gradient slot
+  long ngacc = 0;  // lines with a gradient slot (the longest of the axes' counts)
 
   // register plan width E of the passes along each axis
   int plan_e[3] = {0, 0, 0};
@@ -794,15 +794,6 @@ long obs_nblocks(const sgp_ctx* c, int axis, int e) {
   return ((nx + W - 1) / W) * nouter;
 }
 
-// Blocks of a pass kernel along `axis` with plan width e (one adjoint slot each).
-long pass_nblocks(const sgp_ctx* c, int axis, int e) {
-  const int nx = c->g.n[0], ny = c->g.n[1], nz = c->g.dim == 3 ? c->g.n[2] : 1;
-  const int W = lines_per_block(c->g.n[axis], e);
-  if (axis == 0) return ((long)ny * nz + W - 1) / W;
-  const long nouter = axis == 1 ? nz : ny;
-  return ((nx + W - 1) / W) * nouter;
-}
-
 template <typename T>
 int observables_impl(sgp_ctx* c, const void* psi, double out[12]) {
   double* part = (double*)c->at(c->off_part);
@@ -1178,19 +1169,17 @@ int sgp_create(const sgp_grid* grid, const sgp_params* params, int dtype, void* 
   c->off_clock = off;
   off += 256;
   c->off_part = off;
-  // block partials and adjoint parameter slots: one per block of the largest pass
-  // over every plan
+  // block partials of the observables: one per block of the largest pass over every plan
   long maxb = 0;
   for (int axis = 0; axis < c->g.dim; ++axis)
     for (int e : plan_widths(c->g.n[axis], (int)c->esize))
-      maxb = std::max(maxb, std::max(obs_nblocks(c, axis, e), pass_nblocks(c, axis, e)));
+      maxb = std::max(maxb, obs_nblocks(c, axis, e));
   off += align256(sizeof(double) * NOBS * maxb);
   c->off_red = off;
   off += align256(sizeof(double) * 3 * NOBS);
-  const long gb = maxb;
-  c->ngacc = gb;
+  c->ngacc = (long)std::max(c->g.n[0], c->g.n[1]) * c->g.n[2];
   c->off_gacc = off;
-  off += align256(sizeof(double) * NGRAD * gb);
+  off += align256(sizeof(double) * NGRAD * c->ngacc);
   c->total = off;
   *out = c;
   return SGP_OK;

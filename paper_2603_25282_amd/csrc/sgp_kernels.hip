@@ -63,20 +63,22 @@ hipError_t launch_obs(int kind, const void* psi, const PassArgs& a, int n, int e
 }
 
 // ---------------------------------------------------------------------------
-// Deterministic sum of block partials: block q adds part[b nq + q] over b; thread t
-// takes b = t, t + 256, ... in order, then a fixed pairwise tree over the threads.
-// The order does not depend on timing, so repeated calls give bitwise equal sums.
+// Deterministic sum of partials: block q adds part[b nq + q] over b; thread t takes
+// b = t, t + 1024, ... in order (four loads in flight), then a fixed pairwise tree over the
+// threads.  The order does not depend on timing, so repeated calls give bitwise equal sums.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ part, long nb, int nq,
-                                                      double* __restrict__ out) {
-  __shared__ double red[256];
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double* __restrict__ part, long nb, int nq,
+                                                              double* __restrict__ out) {
+  __shared__ double red[kSumThreads];
   const int q = blockIdx.x, t = threadIdx.x;
   double s = 0.0;
-  for (long b = t; b < nb; b += 256) s += part[b * nq + q];
+#pragma unroll 4
+  for (long b = t; b < nb; b += kSumThreads) s += part[b * nq + q];
   red[t] = s;
   __syncthreads();
 #pragma unroll
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = kSumThreads / 2; w > 0; w >>= 1) {
     if (t < w) red[t] += red[t + w];
     __syncthreads();
   }
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__
 }
 
 hipError_t launch_sum_partials(const double* part, long nb, int nq, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)nq), dim3(256), 0, st, part, nb, nq, out);
+  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)nq), dim3(kSumThreads), 0, st, part, nb, nq, out);
   return hipGetLastError();
 }
 

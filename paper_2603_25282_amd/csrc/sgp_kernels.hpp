@@ -63,7 +63,7 @@ struct PassArgs {
   // adjoint support
   void* store;           // forward: where to write the pointwise-stage input (or null)
   const void* fwd;       // adjoint: the stored pointwise-stage input of the forward pass
-  double* gacc;          // adjoint: per-block parameter slots [block][NGRAD], accumulated
+  double* gacc;          // adjoint: per-line parameter slots [line][NGRAD], accumulated
   // rotation mapping
   double shear;          // shear coefficient a: f(x, y) <- f(x + a y, y) (x) or f(x, y + a x) (y)
   double cphase;         // component phase: psi_l *= exp(i l cphase) when cphase_on

@@ -55,12 +55,11 @@ static hipError_t line_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hi
 }
 
 // Lines per block: Geo's W, or one line where that would leave CUs without a block
-// (fewer than 256 blocks).  The arithmetic of a line does not depend on W; the adjoint
-// passes keep Geo's W, which fixes the grouping of their parameter partials.
+// (fewer than 256 blocks).  Nothing of a line's arithmetic depends on W.
 template <typename T, int N, int E, int KIND>
 static hipError_t pass_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
   constexpr int W = Geo<N, E>::W;
-  if constexpr (W > 1 && !KindInfo<KIND>::ADJ) {
+  if constexpr (W > 1) {
     if (pass_blocks<W, KIND>(a) < 256) return pass_w<T, N, E, 1, KIND>(psi, a, st, ev);
   }
   return pass_w<T, N, E, W, KIND>(psi, a, st, ev);

@@ -158,10 +158,18 @@ __device__ __forceinline__ int pass_point(int i, int tid) {
   return i * NT + tid;
 }
 
+// Adjoint passes: the points of a line belong to the line's own 5 TL threads, so that its
+// parameter partials do not depend on the number of lines in the block.
+template <int N, int TL>
+__device__ __forceinline__ int adj_point(int i, int tid) {
+  const int g = tid / (5 * TL), j = tid - g * 5 * TL + i * 5 * TL;
+  return j < N ? g * N + j : 1 << 30;
+}
+
 // Body of one block of a pass over `tile` (W lines), with caller-provided LDS.
 template <typename T, int N, int E, int W, int KIND>
 __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArgs& a, long tile, cx<T>* lx,
-                                          cx<T>* ltw, double (*gred)[NGRAD]) {
+                                          cx<T>* ltw) {
   constexpr int TL = N / E;
   constexpr int NT = W * 5 * TL;
   constexpr int LS = PadLine<N>::size;
@@ -229,7 +237,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   // of them in the same phase) they are loaded here, under the state loads; with more
   // lines per block other wavefronts cover the loads at their place of use, and the
   // registers are worth more.
-  constexpr int PP = (W * N + NT - 1) / NT;  // points per thread
+  constexpr int PP = (E + 4) / 5;  // points per thread
   constexpr bool PRE = !XL && PW && W == 1;
   [[maybe_unused]] constexpr int UN = PRE ? PP : 1;
   T pcs[PRE ? PP : 1][2];
@@ -241,7 +249,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
     pka = reinterpret_cast<const cx<T>*>(a.kin_a)[kx0];
 #pragma unroll
     for (int i = 0; i < PP; ++i) {
-      const int p = pass_point<T, W * N, NT>(i, tid);
+      const int p = ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid);
       const int pt = p < N ? p : 0;
       pcs[i][0] = cs[2 * pt];
       pcs[i][1] = cs[2 * pt + 1];
@@ -327,7 +335,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const int izl = a.dim == 3 ? line0 / a.ny : 0;
       const int iy0 = line0 - izl * a.ny;
       const int iz0 = izl + a.z0;
-      auto point = [&](int i) { return pass_point<T, W * N, NT>(i, tid); };
+      auto point = [&](int i) { return ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid); };
       for (int i = 0, pt = point(0); pt < W * N; pt = point(++i)) {
         const int pc = pt / N, j = pt % N;
         const int line = (int)line0 + pc;  // y + ny z (< 2^31 for every supported grid)
@@ -376,7 +384,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const int nxx = (int)a.ncols;
 #pragma unroll UN
       for (int i = 0; i < PP; ++i) {
-        const int pt = pass_point<T, W * N, NT>(i, tid);
+        const int pt = ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid);
         if (pt >= W * N) break;
         const int pc = pt / N, kl = pt % N;
         const int kx = kx0 + pc < nxx ? kx0 + pc : 0;
@@ -468,19 +476,38 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
   if constexpr (KIND == C_PROP || KIND == C_ADJ) fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
 
   if constexpr (ADJ) {
-    // parameter partials: block reduction in a fixed order into this block's slot
+    // parameter partials: each line's sum over its threads, in an order that depends on the
+    // plan only, into the line's slot.  Through LDS (free after the transform): kH strided
+    // partial sums per line and parameter, then their sum.
+    constexpr int Q0 = XADJ ? 1 : 0, NQ = XADJ ? 4 : 2, kH = 16;  // parameters Q0 .. Q0 + NQ - 1
+    static_assert(sizeof(double) * NQ * NT <= sizeof(cx<T>) * pass_lds<N, W, KIND>(), "partials fit the tile");
+    double* red = reinterpret_cast<double*>(lx);
+    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NGRAD; ++q) {
-      double vq = gacc[q];
+    for (int q = 0; q < NQ; ++q) red[q * NT + tid] = gacc[Q0 + q];
+    __syncthreads();
+    constexpr int NU = W * NQ * kH, RU = (NU + NT - 1) / NT;
+    double part[RU];
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) vq += __shfl_down(vq, off, 64);
-      if ((tid & 63) == 0) gred[tid >> 6][q] = vq;
+    for (int i = 0; i < RU; ++i) {
+      const int u = tid + i * NT, g = u / (NQ * kH), q = u / kH % NQ, h = u % kH;
+      double sum = 0.0;
+      if (u < NU)
+        for (int k = h; k < 5 * TL; k += kH) sum += red[q * NT + g * 5 * TL + k];
+      part[i] = sum;
     }
     __syncthreads();
-    if (tid < NGRAD) {
+#pragma unroll
+    for (int i = 0; i < RU; ++i)
+      if (tid + i * NT < NU) red[tid + i * NT] = part[i];
+    __syncthreads();
+    for (int u = tid; u < W * NQ; u += NT) {
+      const int g = u / NQ, q = u % NQ;
       double sum = 0.0;
-      for (int wv = 0; wv < (NT + 63) / 64; ++wv) sum += gred[wv][tid];
-      a.gacc[(long)tile * NGRAD + tid] += sum;  // one slot per tile of the instance
+#pragma unroll
+      for (int h = 0; h < kH; ++h) sum += red[u * kH + h];
+      const long slot = XL ? (long)line0 + g : (long)o * a.ncols + kx0 + g;
+      if (FULL || (XL ? line0 + g < a.nlines : kx0 + g < a.ncols)) a.gacc[slot * NGRAD + Q0 + q] += sum;
     }
   }
 
@@ -510,7 +537,6 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ ps
   constexpr int TWB = (pass_tw<N, E, KIND>() * (int)sizeof(cx<T>) + 15) / 16;
   __shared__ cx<T> lx[BUF];
   __shared__ uint4 ltw[TWB > 0 ? TWB : 1];
-  __shared__ double gred[KindInfo<KIND>::ADJ ? NT / 64 + 1 : 1][NGRAD];
   long nb = gridDim.x;
   if constexpr (KIND == C_PROP || KIND == C_KIN) {
     if (a.advance_clock) {
@@ -521,7 +547,7 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ ps
       }
     }
   }
-  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, nb), lx, reinterpret_cast<cx<T>*>(ltw), gred);
+  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, nb), lx, reinterpret_cast<cx<T>*>(ltw));
 }
 
 // ---------------------------------------------------------------------------
@@ -561,7 +587,6 @@ __global__ __launch_bounds__(320) void k_pass_batched(const int2* __restrict__ i
   __shared__ cx<T> lx[BUF > 0 ? BUF : 1];
   __shared__ uint4 ltwr[TWB > 0 ? TWB : 1];
   cx<T>* ltw = reinterpret_cast<cx<T>*>(ltwr);
-  __shared__ double gred[KindInfo<KIND>::ADJ ? 6 : 1][NGRAD];
   const int2 it = items[blockIdx.x];
   const PassArgs& a = args[it.x];
   if constexpr (KIND == C_PROP) {
@@ -571,7 +596,7 @@ __global__ __launch_bounds__(320) void k_pass_batched(const int2* __restrict__ i
 #define SGP_BCASE(NN)                                                                                  \
   case NN:                                                                                             \
     if constexpr (NN <= NMAX && batched_plan_ok(NN, E, ES))                                            \
-      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw, gred);                  \
+      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw);                        \
     break;
   switch (a.n_line) {
     SGP_BCASE(64) SGP_BCASE(128) SGP_BCASE(192) SGP_BCASE(256) SGP_BCASE(384) SGP_BCASE(512) SGP_BCASE(768)
