@@ -1475,8 +1475,10 @@ struct sgp_ensemble {
   // partitions: the instances sharing an (x, y) plan-width pair, contiguous in both
   // lists; each partition's launches run on their own stream (one batched launch
   // per pass and partition)
-  size_t off_items[2] = {0, 0}, off_args = 0;
-  struct Part { int ex, ey, nmax; long off[2], n[2]; };
+  // and, where a partition's lines along an axis run the line kernels, its block items
+  // (instance, group of kLineWaves tiles) in a list of their own
+  size_t off_items[2] = {0, 0}, off_litems[2] = {0, 0}, off_args = 0;
+  struct Part { int ex, ey, nmax; long off[2], n[2], loff[2], ln[2]; };
   std::vector<Part> parts;
   char* ws = nullptr;
   // argument slots of a step (per instance one PassArgs each): the first X-pass,
@@ -1665,48 +1667,73 @@ hipError_t ens_build_items(sgp_ensemble* e) {
   std::sort(pairs.begin(), pairs.end());
   e->parts.clear();
   for (const auto& wp : pairs) {
-    sgp_ensemble::Part P{wp.first, wp.second, 0, {0, 0}, {0, 0}};
+    sgp_ensemble::Part P{wp.first, wp.second, 0, {0, 0}, {0, 0}, {0, 0}, {0, 0}};
     for (auto* c : e->ctx)
       if (c->plan_e[0] == P.ex && c->plan_e[1] == P.ey) P.nmax = std::max(P.nmax, c->g.n[0]);
     e->parts.push_back(P);
   }
+  // block b of a launch runs on XCD b % 8: give each XCD one contiguous range of the
+  // partition's items (XCD j gets n/8 items, one more when j < n % 8), so neighbouring
+  // tiles, which share cache lines, share that XCD's L2
+  auto xcd_order = [](std::vector<int2>& items, long off, long n) {
+    std::vector<int2> perm(n);
+    for (long b = 0; b < n; ++b) {
+      const long j = b % 8, start = j * (n / 8) + std::min(j, n % 8);
+      perm[b] = items[off + start + b / 8];
+    }
+    std::copy(perm.begin(), perm.end(), items.begin() + off);
+  };
   for (int ax = 0; ax < 2; ++ax) {
-    std::vector<int2> items;
+    std::vector<int2> items, litems;
     for (auto& P : e->parts) {
       const int w = ax == 0 ? P.ex : P.ey;
       P.off[ax] = (long)items.size();
+      P.loff[ax] = (long)litems.size();
+      long pts = 0;
+      for (auto* c : e->ctx)
+        if (c->plan_e[0] == P.ex && c->plan_e[1] == P.ey) pts += c->npts();
+      // the line kernels from the number of points at which single 3D grids take them
+      const int esize = (int)e->ctx[0]->esize;
+      const bool line = batched_line_plan(w, esize) && pts >= line_points_min(esize);
       for (int i = 0; i < e->n; ++i) {
         if (e->ctx[i]->plan_e[0] != P.ex || e->ctx[i]->plan_e[1] != P.ey) continue;
-        const long nt = ens_tiles(e->ctx[i]->g.n[0], w);
+        const int n = e->ctx[i]->g.n[0];
+        const long nt = ens_tiles(n, w);
         for (long t = 0; t < nt; ++t) items.push_back(make_int2(i, (int)t));
+        for (int t = 0; line && t < line_blocks(n, w); ++t) litems.push_back(make_int2(i, t));
       }
       P.n[ax] = (long)items.size() - P.off[ax];
-      // block b of a launch runs on XCD b % 8: give each XCD one contiguous range of
-      // the partition's items (XCD j gets n/8 items, one more when j < n % 8), so
-      // neighbouring tiles, which share cache lines, share that XCD's L2
-      const long n = P.n[ax];
-      std::vector<int2> perm(n);
-      for (long b = 0; b < n; ++b) {
-        const long j = b % 8, start = j * (n / 8) + std::min(j, n % 8);
-        perm[b] = items[P.off[ax] + start + b / 8];
-      }
-      std::copy(perm.begin(), perm.end(), items.begin() + P.off[ax]);
+      P.ln[ax] = (long)litems.size() - P.loff[ax];
+      xcd_order(items, P.off[ax], P.n[ax]);
+      xcd_order(litems, P.loff[ax], P.ln[ax]);
     }
     hipError_t r = hipMemcpyAsync(e->ws + e->off_items[ax], items.data(), sizeof(int2) * items.size(),
                                   hipMemcpyHostToDevice, e->st);
+    if (r == hipSuccess && !litems.empty())
+      r = hipMemcpyAsync(e->ws + e->off_litems[ax], litems.data(), sizeof(int2) * litems.size(), hipMemcpyHostToDevice,
+                         e->st);
+    if (r == hipSuccess) r = hipStreamSynchronize(e->st);
     if (r != hipSuccess) return r;
   }
-  return hipStreamSynchronize(e->st);
+  return hipSuccess;
+}
+
+// The batched launch of a pass over partition P: its line kernels' items where it has them.
+template <typename T>
+hipError_t ens_launch(sgp_ensemble* e, const sgp_ensemble::Part& P, hipStream_t st, int kind, const PassArgs* args) {
+  const int ax = (kind == C_PROP || kind == C_ADJ) ? 1 : 0;
+  const int w = ax == 0 ? P.ex : P.ey;
+  if (P.ln[ax] > 0 && (kind == X_FIRST || kind == X_MID || kind == X_LAST || kind == C_PROP))
+    return launch_line_batched<T>(kind, w, (const int2*)(e->ws + e->off_litems[ax]) + P.loff[ax], args, P.ln[ax], st);
+  return launch_pass_batched<T>(kind, w, (const int2*)(e->ws + e->off_items[ax]) + P.off[ax], args, P.n[ax], P.nmax,
+                                st);
 }
 
 // One slot's batched pass over the instances of partition P, on stream st.
 template <typename T>
 hipError_t ens_launch_part(sgp_ensemble* e, const sgp_ensemble::Part& P, hipStream_t st, int slot) {
   const PassArgs* args = (const PassArgs*)(e->ws + e->off_args) + (size_t)slot * e->n;
-  const int kind = e->slots[slot].kind;
-  const int ax = kind == C_PROP ? 1 : 0;
-  const int2* items = (const int2*)(e->ws + e->off_items[ax]);
-  return launch_pass_batched<T>(kind, ax == 0 ? P.ex : P.ey, items + P.off[ax], args, P.n[ax], P.nmax, st);
+  return ens_launch<T>(e, P, st, e->slots[slot].kind, args);
 }
 
 // Run fn(partition, stream) for every partition, each on its own stream, between one
@@ -1894,12 +1921,8 @@ int ens_adjoint_run(sgp_ensemble* e, void* const* states, long nsteps, char* sto
   const PassArgs* args = (const PassArgs*)store;
   r = ens_fork_run(e, e->st, [&](const sgp_ensemble::Part& P, hipStream_t sst) {
     hipError_t rr = hipSuccess;
-    for (size_t L = 0; L < kinds.size() && rr == hipSuccess; ++L) {
-      const int ax = (kinds[L] == C_PROP || kinds[L] == C_ADJ) ? 1 : 0;
-      const int2* items = (const int2*)(e->ws + e->off_items[ax]);
-      rr = launch_pass_batched<T>(kinds[L], ax == 0 ? P.ex : P.ey, items + P.off[ax], args + L * e->n, P.n[ax],
-                                  P.nmax, sst);
-    }
+    for (size_t L = 0; L < kinds.size() && rr == hipSuccess; ++L)
+      rr = ens_launch<T>(e, P, sst, kinds[L], args + L * e->n);
     return rr;
   });
   if (r != hipSuccess) return efail(e, SGP_ERR_HIP, std::string("batched launch: ") + hipGetErrorString(r));
@@ -1949,6 +1972,8 @@ int sgp_ensemble_create(int n_inst, const sgp_grid* grids, const sgp_params* par
   }
   for (int ax = 0; ax < 2; ++ax) {
     e->off_items[ax] = off;
+    off += align256(sizeof(int2) * cap);
+    e->off_litems[ax] = off;
     off += align256(sizeof(int2) * cap);
   }
   e->off_args = off;

@@ -35,6 +35,22 @@ hipError_t launch_pass(int kind, void* psi, const PassArgs& a, int n, int e, hip
   extern template hipError_t launch_line_e<TT, EE>(int, void*, const PassArgs&, int, hipStream_t, const hipEvent_t*);
 SGP_EXTERN_L(float, 4) SGP_EXTERN_L(float, 8) SGP_EXTERN_L(float, 12) SGP_EXTERN_L(double, 4) SGP_EXTERN_L(double, 8)
 #undef SGP_EXTERN_L
+extern template hipError_t launch_line_batched_e<float, 4>(int, const int2*, const PassArgs*, long, hipStream_t);
+extern template hipError_t launch_line_batched_e<float, 12>(int, const int2*, const PassArgs*, long, hipStream_t);
+extern template hipError_t launch_line_batched_e<double, 4>(int, const int2*, const PassArgs*, long, hipStream_t);
+
+template <typename T>
+hipError_t launch_line_batched(int kind, int e, const void* items, const void* args, long nitems, hipStream_t st) {
+  const int2* it = (const int2*)items;
+  const PassArgs* ar = (const PassArgs*)args;
+  if (nitems <= 0) return hipSuccess;
+  if (e == 4) return launch_line_batched_e<T, 4>(kind, it, ar, nitems, st);
+  if constexpr (sizeof(T) == 4)
+    if (e == 12) return launch_line_batched_e<T, 12>(kind, it, ar, nitems, st);
+  return hipErrorInvalidValue;
+}
+template hipError_t launch_line_batched<float>(int, int, const void*, const void*, long, hipStream_t);
+template hipError_t launch_line_batched<double>(int, int, const void*, const void*, long, hipStream_t);
 
 template <typename T>
 hipError_t launch_line(int kind, void* psi, const PassArgs& a, int n, int e, hipStream_t st, const hipEvent_t* ev) {

@@ -124,6 +124,16 @@ constexpr bool line_ok(int n, int e, int esize) {
                 : (e == 12 && esize == 4 && (n == 192 || n == 384 || n == 768));
 }
 
+// Plans whose line kernels an ensemble partition can run (for every length of that width).
+constexpr bool batched_line_plan(int e, int esize) { return e == 4 || (e == 12 && esize == 4); }
+// wavefront tiles per block of a line kernel
+constexpr int kLineWaves = 4;
+constexpr int line_blocks(int n, int e) { return n / (64 / (n / e)) / kLineWaves; }  // of a 2D n x n grid
+template <typename T>
+hipError_t launch_line_batched(int kind, int e, const void* items, const void* args, long nitems, hipStream_t st);
+template <typename T, int E>
+hipError_t launch_line_batched_e(int kind, const int2* items, const PassArgs* args, long nitems, hipStream_t st);
+
 // ev: null, or a start / end event pair stamped by the kernel's dispatch
 template <typename T>
 hipError_t launch_line(int kind, void* psi, const PassArgs& a, int n, int e, hipStream_t st,

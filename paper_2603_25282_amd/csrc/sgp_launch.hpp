@@ -128,6 +128,22 @@ hipError_t launch_line_e(int kind, void* psi, const PassArgs& a, int n, hipStrea
   return hipErrorInvalidValue;
 }
 
+template <typename T, int E>
+hipError_t launch_line_batched_e(int kind, const int2* it, const PassArgs* ar, long nitems, hipStream_t st) {
+  if constexpr (batched_line_plan(E, (int)sizeof(T))) {
+    dim3 g((unsigned)nitems), b(64 * kLineWaves);
+    switch (kind) {
+      case X_FIRST: hipLaunchKernelGGL((k_line_batched<T, X_FIRST, E>), g, b, 0, st, it, ar); break;
+      case X_MID: hipLaunchKernelGGL((k_line_batched<T, X_MID, E>), g, b, 0, st, it, ar); break;
+      case X_LAST: hipLaunchKernelGGL((k_line_batched<T, X_LAST, E>), g, b, 0, st, it, ar); break;
+      case C_PROP: hipLaunchKernelGGL((k_line_batched<T, C_PROP, E>), g, b, 0, st, it, ar); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
 // Batched passes of one plan width (compiled with that width's unit).
 template <typename T, int E, int NMAX>
 static hipError_t launch_batched_nmax(int kind, const int2* it, const PassArgs* ar, long nitems, hipStream_t st) {

@@ -16,9 +16,8 @@
 
 namespace sgp {
 
-// Wavefronts per block (they share the staged twiddles).  Two: x 54.0 instead of 51.0 us
-// at 128^3; eight: 58.8.
-constexpr int kLineWaves = 4;
+// kLineWaves wavefronts per block (they share the staged twiddles): four.  Two: x 54.0
+// instead of 51.0 us at 128^3; eight: 58.8.
 
 // Wavefronts per SIMD to keep room for: 80 registers of state come out at 150 to 175 in
 // all, and above 168 (two wavefronts) the 192x128x64 complex128 y-pass takes 70 instead of
@@ -45,29 +44,17 @@ __device__ __forceinline__ void line_reorder(cx<T> (&v)[5][E], int m, cx<T>* lx,
   for (int i = 0; i < 5; ++i) v[i][m] = lx[IN ? lane * 5 + i : i * 64 + lane];
 }
 
+// One wavefront's tile of a line pass: 64/TL lines; xch: the wavefront's LDS, ltw: the
+// block's table.
 template <typename T, int N, int E, int KIND>
-__global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T))) void k_line(cx<T>* __restrict__ psi, PassArgs a) {
+__device__ __forceinline__ void line_body(cx<T>* __restrict__ psi, const PassArgs& a, int tile, cx<T>* xch,
+                                          cx<T>* ltw) {
   constexpr int TL = N / E;
   constexpr int W = 64 / TL;  // lines per wavefront
   constexpr int LS = PadLine<N>::size;
   constexpr bool XL = KindInfo<KIND>::XL;
   constexpr int TW = pass_tw<N, E, KIND>();
-  __shared__ cx<T> xch[kLineWaves][line_lds<N, E>()];
-  __shared__ uint4 ltwr[(TW * (int)sizeof(cx<T>) + 15) / 16];
-  cx<T>* ltw = reinterpret_cast<cx<T>*>(ltwr);
-
-  long nb = gridDim.x;
-  if constexpr (KIND == C_PROP || KIND == C_KIN) {
-    if (a.advance_clock) {
-      nb -= 1;
-      if (blockIdx.x == nb) {
-        if (threadIdx.x == 0) advance_clock(a);
-        return;
-      }
-    }
-  }
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int tile = (int)xcd_tile(blockIdx.x, nb) * kLineWaves + wave;
+  const int lane = threadIdx.x & 63;
   // x-lines: the threads of a line are adjacent; columns: the W columns are
   const int col = XL ? lane / TL : lane % W;
   const int t = XL ? lane % TL : lane / W;
@@ -91,7 +78,7 @@ __global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T)))
     const int e = i * 64 + lane;
     off[i] = (uint32_t)(((long)(e / RL) * pitch + e % RL) * (int)sizeof(cx<T>));
   }
-  cx<T>* lx0 = xch[wave];
+  cx<T>* lx0 = xch;
   TwStage<T, 64 * kLineWaves, TW> stage;
   stage.load(a.tw, threadIdx.x);
   cx<T> v[5][E];
@@ -204,6 +191,64 @@ __global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T)))
       a.clock[2] = st;
     }
   }
+}
+
+template <typename T, int N, int E, int KIND>
+__global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T))) void k_line(cx<T>* __restrict__ psi,
+                                                                                          PassArgs a) {
+  __shared__ cx<T> xch[kLineWaves][line_lds<N, E>()];
+  __shared__ uint4 ltw[(pass_tw<N, E, KIND>() * (int)sizeof(cx<T>) + 15) / 16];
+  long nb = gridDim.x;
+  if constexpr (KIND == C_PROP || KIND == C_KIN) {
+    if (a.advance_clock) {
+      nb -= 1;
+      if (blockIdx.x == nb) {
+        if (threadIdx.x == 0) advance_clock(a);
+        return;
+      }
+    }
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  line_body<T, N, E, KIND>(psi, a, (int)xcd_tile(blockIdx.x, nb) * kLineWaves + wave, xch[wave],
+                           reinterpret_cast<cx<T>*>(ltw));
+}
+
+// Line pass over many grids (an ensemble's partition, see k_pass_batched): block b processes
+// work item items[b] = (instance, group of kLineWaves tiles).
+template <int N, int E, int KIND, int ES>
+constexpr int batched_line_tw() {
+  if constexpr (line_ok(N, E, ES)) return pass_tw<N, E, KIND>();
+  else return 0;
+}
+template <typename T, int KIND, int E>
+__global__ __launch_bounds__(64 * kLineWaves, line_min_waves(E, (int)sizeof(T))) void k_line_batched(
+    const int2* __restrict__ items, const PassArgs* __restrict__ args) {
+  constexpr int ES = (int)sizeof(T);
+  constexpr int BUF = E == 4 ? cmax(cmax(line_lds<64, 4>(), line_lds<128, 4>()), line_lds<256, 4>())
+                             : cmax(cmax(line_lds<192, 12>(), line_lds<384, 12>()), line_lds<768, 12>());
+  constexpr int TWM = cmax(cmax(cmax(batched_line_tw<64, E, KIND, ES>(), batched_line_tw<128, E, KIND, ES>()),
+                                cmax(batched_line_tw<192, E, KIND, ES>(), batched_line_tw<256, E, KIND, ES>())),
+                           cmax(batched_line_tw<384, E, KIND, ES>(), batched_line_tw<768, E, KIND, ES>()));
+  __shared__ cx<T> xch[kLineWaves][BUF];
+  __shared__ uint4 ltwr[(TWM * (int)sizeof(cx<T>) + 15) / 16];
+  cx<T>* ltw = reinterpret_cast<cx<T>*>(ltwr);
+  const int2 it = items[blockIdx.x];
+  const PassArgs& a = args[it.x];
+  if constexpr (KIND == C_PROP) {
+    if (a.advance_clock && it.y == 0 && threadIdx.x == 64 * kLineWaves - 1) advance_clock(a);
+  }
+  cx<T>* psi = reinterpret_cast<cx<T>*>(a.state);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = it.y * kLineWaves + wave;
+#define SGP_LCASE(NN)                                                                              \
+  case NN:                                                                                         \
+    if constexpr (line_ok(NN, E, ES)) line_body<T, NN, E, KIND>(psi, a, tile, xch[wave], ltw);      \
+    break;
+  switch (a.n_line) {
+    SGP_LCASE(64) SGP_LCASE(128) SGP_LCASE(192) SGP_LCASE(256) SGP_LCASE(384) SGP_LCASE(768)
+    default: break;
+  }
+#undef SGP_LCASE
 }
 
 }  // namespace sgp

@@ -14,6 +14,7 @@ template hipError_t launch_line_e<SGP_INST_T, SGP_INST_E>(int, void*, const Pass
                                                            const hipEvent_t*);
 template hipError_t launch_obs_e<SGP_INST_T, SGP_INST_E>(int, const void*, const PassArgs&, int, double*,
                                                          hipStream_t);
+template hipError_t launch_line_batched_e<SGP_INST_T, SGP_INST_E>(int, const int2*, const PassArgs*, long, hipStream_t);
 template hipError_t launch_batched_e<SGP_INST_T, SGP_INST_E>(int, const int2*, const PassArgs*, long, int,
                                                              hipStream_t);
 }  // namespace sgp
