@@ -243,7 +243,11 @@ int sgp_time_pass(sgp_ctx* ctx, void* psi_dev, int pass, int reps, double* avg_m
  *   elems = 0 restores the default.  SGP_ERR_ARG if the width is not available
  *   for that axis's length.  Rewrites the twiddle tables in the workspace (if set)
  *   and drops the captured step graph; call it between steps, not concurrently
- *   with work on the context's stream.
+ *   with work on the context's stream.  3D grids of 2^20 (SGP_C64) or 2^19 (SGP_C128)
+ *   points and more run some passes of a step on kernels with a width of their own
+ *   (chosen by line length, element type and number of points); along such an axis the
+ *   plan's width applies to the adjoint, observables, rotation-map and lab-frame
+ *   transform passes only.
  * sgp_get_plan: the current width of `axis`.
  * Pseudo-axis SGP_PLAN_LINEAR (3D contexts only; SGP_ERR_ARG otherwise): the order of
  *   a linear substep's two passes.  The propagator of eq. sl1 is the product of its part
@@ -255,7 +259,8 @@ int sgp_time_pass(sgp_ctx* ctx, void* psi_dev, int pass, int reps, double* avg_m
  *   adjoint) always uses order 0.
  * sgp_autotune: picks the fastest combination of the axes' widths (every
  *   combination, at most 9 in 2D and 27 in 3D, in 3D for both linear-substep
- *   orders) by timing `steps` steps of the
+ *   orders; an axis whose pass of a step has a width of its own, see sgp_set_plan,
+ *   keeps its plan) by timing `steps` steps of the
  *   sgp_step path for each, after one untimed call of `steps` steps; psi_dev is
  *   a device state in the layout of sgp_step; it is advanced by every timed and
  *   untimed step (pass a scratch copy).  Needs the workspace and the propagator;

@@ -716,8 +716,8 @@ int set_plan_impl(sgp_ctx* c, int axis, int e) {
 }
 
 // Autotuner: time `steps` whole steps (the sgp_step path, graphs included) for
-// every combination of the axes' plan widths (in 3D also both linear-substep
-// splits) and keep the fastest.  psi is advanced by the timed steps; the context time
+// every combination of the plan widths that the step uses (in 3D also both orders of
+// the linear substep) and keep the fastest.  psi is advanced by the timed steps; the context time
 // is restored.
 template <typename T>
 int autotune_impl(sgp_ctx* c, void* psi, int steps, int out_e[3], double* best_ms) {
@@ -748,7 +748,11 @@ int autotune_impl(sgp_ctx* c, void* psi, int steps, int out_e[3], double* best_m
   double best = 0.0;
   int rc = time_steps(&best);
   std::vector<int> w[3];
-  for (int ax = 0; ax < 3; ++ax) w[ax] = ax < c->g.dim ? plan_widths(c->g.n[ax], (int)c->esize) : std::vector<int>{0};
+  // (an axis whose pass of a step runs on the line kernel keeps its width: the step does not
+  // use it, equal candidates would be told apart by noise, and the adjoint and observables
+  // passes would run at the winner's width)
+  for (int ax = 0; ax < 3; ++ax)
+    w[ax] = ax >= c->g.dim || c->line_e[ax] ? std::vector<int>{c->plan_e[ax]} : plan_widths(c->g.n[ax], (int)c->esize);
   int best_e[3] = {c->plan_e[0], c->plan_e[1], c->plan_e[2]};
   int best_ls = c->lin_split;
   const int start[3] = {c->plan_e[0], c->plan_e[1], c->plan_e[2]};

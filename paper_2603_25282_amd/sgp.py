@@ -295,7 +295,8 @@ class Solver:
         return f"{arch}|{'x'.join(map(str, self.shape))}|{str(self.torch_dtype).replace('torch.', '')}|TS{scheme}"
 
     def autotune(self, psi, scheme, steps=20, cache=True):
-        """Pick the plan width of every axis (sgp_autotune on a scratch copy of psi)
+        """Pick the plan width of every axis that the step uses one on (sgp_autotune on
+        a scratch copy of psi; the other axes keep theirs)
         and keep the choice in the JSON plan cache (plan_cache_path()); with cache,
         a stored choice for this device, shape, dtype and scheme is applied without
         timing.  Returns (widths, ms_per_step or None)."""
