@@ -95,27 +95,46 @@ constexpr int obs_lines_per_block(int n, int e) {
 
 // The line kernels (sgp_lines.hpp: five components per thread): points per thread of a
 // pass over lines of length n of a 3D grid of npts points, or 0 where the component-split
-// kernel of the axis's plan runs.  Measured (in-step, complex64 unless noted, component-
-// split with its best width against the line kernel):
-//   * small grids have too few lines: 64^3 x 11.9 against 14.9 us, 128x64x64 17.9 against
-//     20.5 (complex128 39.7 against 27.5); 128^3: x 57.7 against 51.0, y 46.1 against 44.1.
+// kernel of the axis's plan runs.  Measured in step, complex64 unless noted, component-split
+// against the line kernel in us (the split one at its default width unless a width is given;
+// shapes nx x ny x nz):
+//   * small grids have too few lines: 64^3 x 11.9 against 14.9, 128x64x64 17.9 against
+//     20.5 (complex128 39.7 against 27.5); 128^3: x 57.7 against 51.0.
+//   * y-lines of 64 to 256 points: below 2^21 points the split kernel is as fast or faster
+//     (64x64x256 21.6 against 22.5, 768x64x32 28.6 / 30.3, 768x128x16 35.3 / 37.1, 384x256x16
+//     35.0 / 37.6), at 2^21 they are equal on average (128^3 42.7 / 43.0, 64x256x128
+//     47.0 / 45.5, 512x64x64 36.9 / 39.4, 256x64x128 37.4 / 35.7), above it the line kernel
+//     (256x64x256 68.7 / 64.2, 128x128x256 82.8 / 80.2, 256x256x64 89.3 / 85.6, 256^3
+//     408 / 395).
 //   * powers of two up to 256 run E = 4 (radix 4, 5 wavefronts per SIMD): with E = 8 the
 //     x-pass takes 52.9 and the y-pass 47.5 at 128^3 (3 wavefronts per SIMD).  512: E = 8,
-//     the widest line that fits a wavefront: x 70.2 against 55.3.
-//   * 3 * 2^k: E = 12 (192^3: x 222 against 179, y 217 against 172, z 157 against 154).
-//   * z-pass (three transforms' worth of traffic and little arithmetic): the
-//     component-split kernel streams faster (128^3 33.1 against 38.0) up to the Infinity
-//     Cache's size; beyond it the line kernel (256^3 355 against 301), and for 384, 768
-//     (47.8 against 40.9).
-//   * complex128: E = 4 (128x128x64: x 48.5 against 39.0, y 62.5 against 43.1, z 47.5
-//     against 37.8), z-lines of 64 stay (28.7 against 32.2); 512: E = 8 (z 53.5 against
-//     40.4); 3 * 2^k would need 240 registers of state.
+//     the widest line that fits a wavefront: x 70.2 against 55.3, y of 64x512x512 441 / 428.
+//   * 3 * 2^k: E = 12 (192^3: x 222 against 179, y 217 against 172; y of 128x384x64
+//     113 / 83).
+//   * z-pass (three transforms' worth of traffic and little arithmetic): the component-split
+//     kernel streams faster while the state fits the Infinity Cache (128^3 32.6 / 39.8, 192^3
+//     136.5 / 142, 256 points at 2^22 68.7 / 77.3, 512 at 2^22 80.3 / 91.5), the line kernel
+//     beyond it, from 2^23 points (192x256x192 205 / 194, 256 points 183 / 165.5, 512 points
+//     271 / 206); 64 and 128 points are as fast or faster split there too (256x256x64 53.0 /
+//     61.0, 256x256x128 157 / 158, 256x512x128 301 / 304), 384 and 768 on the line kernel
+//     everywhere (64x64x384 47.0 / 39.2, 32x64x768 46.9 / 43.2).
+//   * complex128: E = 4 (128x128x64: x 48.5 against 39.0, y 62.5 against 43.1); z-lines of
+//     64 stay (192x128x64 42.6 / 48.8).  z-lines of 128 and 256 within the cache are faster
+//     split with E = 4 (64x128x128 33.6 / 38.1, 64x64x256 35.8 / 37.7) but not at the default
+//     width that untuned programs run (whole TS2 step of 64x128x128 126.2 / 123.9, of
+//     64x64x128 74.6 / 73.5; z of 64x64x256 51.7 / 37.7), so they run the line kernel, as
+//     beyond the cache (256x128x128 157 / 141).  512: E = 8 (32x64x512 50.5 / 39.1);
+//     3 * 2^k would need 240 registers of state.
 constexpr long line_points_min(int esize) { return esize == 4 ? 1L << 20 : 1L << 19; }
 constexpr int line_elems(int kind, int n, int esize, long npts) {
-  const bool z = kind == C_KIN, p2 = n == 64 || n == 128 || n == 256;
-  if (npts < line_points_min(esize) || !(kind == X_FIRST || kind == X_MID || kind == X_LAST || kind == C_PROP || z)) return 0;
+  const bool y = kind == C_PROP, z = kind == C_KIN, p2 = n == 64 || n == 128 || n == 256;
+  if (npts < line_points_min(esize) || !(kind == X_FIRST || kind == X_MID || kind == X_LAST || y || z)) return 0;
   if (esize == 8) return p2 ? (z && n == 64 ? 0 : 4) : n == 512 ? 8 : 0;
-  if (z) return n == 256 && npts >= (1L << 23) ? 8 : (n == 384 || n == 768) ? 12 : 0;
+  if (z) {
+    const bool beyond = npts >= 1L << 23;  // a state larger than the Infinity Cache
+    return (n == 256 || n == 512) && beyond ? 8 : n == 384 || n == 768 || (n == 192 && beyond) ? 12 : 0;
+  }
+  if (y && p2 && npts < 1L << 21) return 0;
   return p2 ? 4 : n == 512 ? 8 : (n == 192 || n == 384 || n == 768) ? 12 : 0;
 }
 // (n, e) pairs with a compiled line kernel
