@@ -158,20 +158,119 @@ __device__ __forceinline__ int pass_point(int i, int tid) {
   return i * NT + tid;
 }
 
-// Adjoint passes: the points of a line belong to the line's own 5 TL threads, so that its
-// parameter partials do not depend on the number of lines in the block.
-template <int N, int TL>
-__device__ __forceinline__ int adj_point(int i, int tid) {
-  const int g = tid / (5 * TL), j = tid - g * 5 * TL + i * 5 * TL;
-  return j < N ? g * N + j : 1 << 30;
+// One level of the tree sums over a wavefront of two values at once, in lane exchanges of the
+// vector unit.  H = 32: a's sums over lanes l, l + 32 in the lower half and b's in the upper;
+// H = 16: a's sums over rows (of 16 lanes) 2 r, 2 r + 1 in row 2 r and b's in row 2 r + 1.
+template <int H>
+__device__ __forceinline__ double half_sums(double a, double b) {
+  uint32_t x[2], y[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t wa = i ? (uint32_t)__double2hiint(a) : (uint32_t)__double2loint(a);
+    const uint32_t wb = i ? (uint32_t)__double2hiint(b) : (uint32_t)__double2loint(b);
+    // a's upper half (odd rows) and b's lower half (even rows) change places
+    const auto r = H == 32 ? __builtin_amdgcn_permlane32_swap(wa, wb, false, false)
+                           : __builtin_amdgcn_permlane16_swap(wa, wb, false, false);
+    x[i] = r[0];
+    y[i] = r[1];
+  }
+  return __hiloint2double((int)x[1], (int)x[0]) + __hiloint2double((int)y[1], (int)y[0]);
 }
 
-// Body of one block of a pass over `tile` (W lines), with caller-provided LDS.
+// The value of lane l + OFF of the row (of no use in the row's last OFF lanes).
+template <int OFF>
+__device__ __forceinline__ double row_down(double a) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(a), 0x100 + OFF, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(a), 0x100 + OFF, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Parameter partials of an adjoint pass, one value per line and parameter (NQ parameters),
+// summed in an order that depends on the line's length only, so that it is the same for any
+// number of lines in a block: every SG consecutive points by a tree (offsets SG/2, ..., 1),
+// then the line's SG-point sums one after the other.  The points go to the threads as in a
+// forward pass.  (Given to their own line's threads, 5 N/E of them, every wavefront of a block
+// had points in the last, partly full round, and the sums took four barriers: a TS2 step of
+// the adjoint 988 instead of 910 us for 96 complex64 grids, 375 instead of 307 at 128^3.)  A
+// block of whole wavefronts runs the tree in registers, the 64 points of a round being one
+// line's, with lane exchanges of the vector unit (through __shfl_down 1012 and 368 us); any
+// other block keeps the points' values in LDS.
+template <int N, int E, int W, int KIND>
+struct GradSum {
+  static constexpr int NT = W * 5 * (N / E), WN = W * N;
+  static constexpr int Q0 = KindInfo<KIND>::XADJ ? 1 : 0, NQ = KindInfo<KIND>::XADJ ? 4 : 2;  // Q0 .. Q0 + NQ - 1
+  static constexpr int SG = N < 64 ? N : 64;
+  static constexpr bool WAVES = NT % 64 == 0;
+  static constexpr int size = !KindInfo<KIND>::ADJ ? 0 : WAVES ? WN / SG * NQ : NQ * WN;
+  static_assert(N % SG == 0 && (!WAVES || WN % 64 == 0), "whole wavefronts of points");
+
+  // the values of point pt (all points of a wavefront at once)
+  static __device__ __forceinline__ void add(double* red, int pt, const double (&v)[NQ]) {
+    if constexpr (WAVES && SG == 64) {
+      // parameters side by side: half a wavefront (two) or a row of 16 lanes (four) each
+      double t;
+      if constexpr (NQ == 4) t = half_sums<16>(half_sums<32>(v[0], v[2]), half_sums<32>(v[1], v[3]));
+      else { t = half_sums<32>(v[0], v[1]); t = half_sums<16>(t, t); }
+      t += row_down<8>(t);
+      t += row_down<4>(t);
+      t += row_down<2>(t);
+      t += row_down<1>(t);
+      constexpr int LQ = 64 / NQ;
+      if (pt % LQ == 0) red[pt / 64 * NQ + pt % 64 / LQ] = t;
+    } else if constexpr (WAVES) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        double t = v[q];
+#pragma unroll
+        for (int off = SG / 2; off > 0; off >>= 1) t += __shfl_down(t, off, SG);
+        if (pt % SG == 0) red[pt / SG * NQ + q] = t;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) red[q * WN + pt] = v[q];
+    }
+  }
+
+  // between two barriers behind the last add: the tree down to 8 values, in their places
+  static __device__ __forceinline__ void fold(double* red, int tid) {
+    if constexpr (!WAVES) {
+      for (int u = tid; u < NQ * WN / SG * 8; u += NT) {
+        double* c = red + u / 8 * SG + u % 8;
+        double t[SG / 8];
+#pragma unroll
+        for (int k = 0; k < SG / 8; ++k) t[k] = c[8 * k];
+#pragma unroll
+        for (int off = SG / 16; off > 0; off >>= 1)
+#pragma unroll
+          for (int k = 0; k < off; ++k) t[k] += t[k + off];
+        c[0] = t[0];
+      }
+    }
+  }
+
+  // after them: the sum of parameter Q0 + q over line g of the block
+  static __device__ __forceinline__ double line(const double* red, int g, int q) {
+    double sum = 0.0;
+    for (int s = 0; s < N / SG; ++s) {
+      if constexpr (WAVES) {
+        sum += red[(g * (N / SG) + s) * NQ + q];
+      } else {
+        const double* c = red + q * WN + g * N + s * SG;
+        sum += ((c[0] + c[4]) + (c[2] + c[6])) + ((c[1] + c[5]) + (c[3] + c[7]));
+      }
+    }
+    return sum;
+  }
+};
+
+// Body of one block of a pass over `tile` (W lines), with caller-provided LDS (red: GradSum's
+// values, adjoint passes only).
 template <typename T, int N, int E, int W, int KIND>
 __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArgs& a, long tile, cx<T>* lx,
-                                          cx<T>* ltw) {
+                                          cx<T>* ltw, [[maybe_unused]] double* red) {
   constexpr int TL = N / E;
   constexpr int NT = W * 5 * TL;
+  using GS = GradSum<N, E, W, KIND>;
   constexpr int LS = PadLine<N>::size;
   constexpr bool XL = KindInfo<KIND>::XL;
   constexpr bool XADJ = KindInfo<KIND>::XADJ;
@@ -249,7 +348,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
     pka = reinterpret_cast<const cx<T>*>(a.kin_a)[kx0];
 #pragma unroll
     for (int i = 0; i < PP; ++i) {
-      const int p = ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid);
+      const int p = pass_point<T, W * N, NT>(i, tid);
       const int pt = p < N ? p : 0;
       pcs[i][0] = cs[2 * pt];
       pcs[i][1] = cs[2 * pt + 1];
@@ -314,7 +413,6 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
         *reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(st + (long)(TL * m) * estride) + so) = v[0][m];
     }
   }
-  double gacc[NGRAD] = {0.0, 0.0, 0.0, 0.0, 0.0};
 
   if constexpr (PW) {
     // to the tile: point (col, j) component c at (col * N + j) * 5 + c
@@ -335,7 +433,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const int izl = a.dim == 3 ? line0 / a.ny : 0;
       const int iy0 = line0 - izl * a.ny;
       const int iz0 = izl + a.z0;
-      auto point = [&](int i) { return ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid); };
+      auto point = [&](int i) { return pass_point<T, W * N, NT>(i, tid); };
       for (int i = 0, pt = point(0); pt < W * N; pt = point(++i)) {
         const int pc = pt / N, j = pt % N;
         const int line = (int)line0 + pc;  // y + ny z (< 2^31 for every supported grid)
@@ -362,12 +460,9 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
           const double dVdO = a.s_arg * (a.g2[0] - a.g2[1]) * X * Y;
           double acc4[4] = {0.0, 0.0, 0.0, 0.0};
           nl_point_adj<T>(q, p, V, dVdO, K, acc4);
-          if (line < a.nlines) {
-            gacc[1] += acc4[0];
-            gacc[2] += acc4[1];
-            gacc[3] += acc4[2];
-            gacc[4] += acc4[3];
-          }
+          if constexpr (!FULL)
+            if (line >= a.nlines) acc4[0] = acc4[1] = acc4[2] = acc4[3] = 0.0;
+          GS::add(red, pt, acc4);
         } else {
           nl_point<T>(p, V, K);
         }
@@ -384,7 +479,7 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const int nxx = (int)a.ncols;
 #pragma unroll UN
       for (int i = 0; i < PP; ++i) {
-        const int pt = ADJ ? adj_point<N, TL>(i, tid) : pass_point<T, W * N, NT>(i, tid);
+        const int pt = pass_point<T, W * N, NT>(i, tid);
         if (pt >= W * N) break;
         const int pc = pt / N, kl = pt % N;
         const int kx = kx0 + pc < nxx ? kx0 + pc : 0;
@@ -418,7 +513,8 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
         if constexpr (KIND == C_ADJ) {
           // P^H = P(-d): same (C - 1), S -> -S, conjugate kinetic phase
           sym4_apply_inc<T>(conj(as), mk<T>(-beta.re, -beta.im), p);
-          if (kx0 + pc < a.ncols) {
+          double acc2[2] = {0.0, 0.0};
+          if (FULL || kx0 + pc < a.ncols) {
             // m_a = -d Im(L^H f_a H), L = P^H L'/N^d (p), H the stored forward input
             const cx<T>* fw = reinterpret_cast<const cx<T>*>(a.fwd) + o * (int)a.outer_stride + kx * 5 + kl * (int)a.stride;
             const double w4[4] = {1.0, 1.22474487139158904909864203735294570, 1.22474487139158904909864203735294570, 1.0};
@@ -452,9 +548,10 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
             const double cx1 = oy * mz - oz * my, cy1 = oz * mx - ox * mz, cz1 = ox * my - oy * mx;
             const double cx2 = oy * cz1 - oz * cy1, cy2 = oz * cx1 - ox * cz1, cz2 = ox * cy1 - oy * cx1;
             const double Dx = mx + ja * cx1 + jb * cx2, Dy = my + ja * cy1 + jb * cy2, Dz = mz + ja * cz1 + jb * cz2;
-            gacc[0] += -nuqd * Dx + nupd * Dy;  // dn/dgamma = (Re a, -Im a, 0) = (-nu_q, nu_p, 0)
-            gacc[1] += -Dz;                     // dn/dOmega = (0, 0, -1)
+            acc2[0] = -nuqd * Dx + nupd * Dy;  // dn/dgamma = (Re a, -Im a, 0) = (-nu_q, nu_p, 0)
+            acc2[1] = -Dz;                     // dn/dOmega = (0, 0, -1)
           }
+          GS::add(red, pt, acc2);
         } else {
           sym4_apply_inc<T>(as, beta, p);
         }
@@ -468,48 +565,20 @@ __device__ __forceinline__ void pass_body(cx<T>* __restrict__ psi, const PassArg
       const int o5 = (col * N + t + TL * m) * 5 + c;
       v[0][m] = lx[o5];
     }
+    if constexpr (ADJ) GS::fold(red, tid);
     __syncthreads();
+  }
+  if constexpr (ADJ) {
+    for (int u = tid; u < W * GS::NQ; u += NT) {
+      const int g = u / GS::NQ, q = u % GS::NQ;
+      const long slot = XL ? (long)line0 + g : (long)o * a.ncols + kx0 + g;
+      if (FULL || (XL ? line0 + g < a.nlines : kx0 + g < a.ncols)) a.gacc[slot * NGRAD + GS::Q0 + q] += GS::line(red, g, q);
+    }
   }
 
   if constexpr (KIND == X_FIRST || KIND == X_MID || KIND == XA_MID || KIND == XA_LAST)
     fft_line<T, N, E, -1, 1, 1, 0>(v, xl, t, tw, 0);
   if constexpr (KIND == C_PROP || KIND == C_ADJ) fft_line<T, N, E, +1, 1, 1, 0>(v, xl, t, tw, 0);
-
-  if constexpr (ADJ) {
-    // parameter partials: each line's sum over its threads, in an order that depends on the
-    // plan only, into the line's slot.  Through LDS (free after the transform): kH strided
-    // partial sums per line and parameter, then their sum.
-    constexpr int Q0 = XADJ ? 1 : 0, NQ = XADJ ? 4 : 2, kH = 16;  // parameters Q0 .. Q0 + NQ - 1
-    static_assert(sizeof(double) * NQ * NT <= sizeof(cx<T>) * pass_lds<N, W, KIND>(), "partials fit the tile");
-    double* red = reinterpret_cast<double*>(lx);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) red[q * NT + tid] = gacc[Q0 + q];
-    __syncthreads();
-    constexpr int NU = W * NQ * kH, RU = (NU + NT - 1) / NT;
-    double part[RU];
-#pragma unroll
-    for (int i = 0; i < RU; ++i) {
-      const int u = tid + i * NT, g = u / (NQ * kH), q = u / kH % NQ, h = u % kH;
-      double sum = 0.0;
-      if (u < NU)
-        for (int k = h; k < 5 * TL; k += kH) sum += red[q * NT + g * 5 * TL + k];
-      part[i] = sum;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RU; ++i)
-      if (tid + i * NT < NU) red[tid + i * NT] = part[i];
-    __syncthreads();
-    for (int u = tid; u < W * NQ; u += NT) {
-      const int g = u / NQ, q = u % NQ;
-      double sum = 0.0;
-#pragma unroll
-      for (int h = 0; h < kH; ++h) sum += red[u * kH + h];
-      const long slot = XL ? (long)line0 + g : (long)o * a.ncols + kx0 + g;
-      if (FULL || (XL ? line0 + g < a.nlines : kx0 + g < a.ncols)) a.gacc[slot * NGRAD + Q0 + q] += sum;
-    }
-  }
 
   if (active) {
     // made opaque: else the addresses of the loads stay in registers (two per value)
@@ -535,8 +604,10 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ ps
   constexpr int BUF = pass_lds<N, W, KIND>();
   constexpr int NT = W * 5 * (N / E);
   constexpr int TWB = (pass_tw<N, E, KIND>() * (int)sizeof(cx<T>) + 15) / 16;
+  constexpr int RED = GradSum<N, E, W, KIND>::size;
   __shared__ cx<T> lx[BUF];
   __shared__ uint4 ltw[TWB > 0 ? TWB : 1];
+  __shared__ double red[RED > 0 ? RED : 1];
   long nb = gridDim.x;
   if constexpr (KIND == C_PROP || KIND == C_KIN) {
     if (a.advance_clock) {
@@ -547,7 +618,7 @@ __global__ __launch_bounds__(W * 5 * (N / E)) void k_pass(cx<T>* __restrict__ ps
       }
     }
   }
-  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, nb), lx, reinterpret_cast<cx<T>*>(ltw));
+  pass_body<T, N, E, W, KIND>(psi, a, xcd_tile(blockIdx.x, nb), lx, reinterpret_cast<cx<T>*>(ltw), red);
 }
 
 // ---------------------------------------------------------------------------
@@ -586,6 +657,8 @@ __global__ __launch_bounds__(320) void k_pass_batched(const int2* __restrict__ i
   constexpr int TWB = (TWM * (int)sizeof(cx<T>) + 15) / 16;
   __shared__ cx<T> lx[BUF > 0 ? BUF : 1];
   __shared__ uint4 ltwr[TWB > 0 ? TWB : 1];
+  // a block's 64 E points (320 threads), in 64-point sums of at most four parameters
+  __shared__ double red[KindInfo<KIND>::ADJ ? 4 * E : 1];
   cx<T>* ltw = reinterpret_cast<cx<T>*>(ltwr);
   const int2 it = items[blockIdx.x];
   const PassArgs& a = args[it.x];
@@ -595,8 +668,10 @@ __global__ __launch_bounds__(320) void k_pass_batched(const int2* __restrict__ i
   cx<T>* psi = reinterpret_cast<cx<T>*>(a.state);
 #define SGP_BCASE(NN)                                                                                  \
   case NN:                                                                                             \
-    if constexpr (NN <= NMAX && batched_plan_ok(NN, E, ES))                                            \
-      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw);                        \
+    if constexpr (NN <= NMAX && batched_plan_ok(NN, E, ES)) {                                          \
+      static_assert(GradSum<NN, E, lines_per_block(NN, E), KIND>::size <= 4 * E, "the sums fit");      \
+      pass_body<T, NN, E, lines_per_block(NN, E), KIND>(psi, a, it.y, lx, ltw, red);                   \
+    }                                                                                                  \
     break;
   switch (a.n_line) {
     SGP_BCASE(64) SGP_BCASE(128) SGP_BCASE(192) SGP_BCASE(256) SGP_BCASE(384) SGP_BCASE(512) SGP_BCASE(768)
