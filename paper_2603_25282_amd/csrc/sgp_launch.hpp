@@ -54,13 +54,18 @@ static hipError_t line_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hi
   return hipGetLastError();
 }
 
-// Lines per block: Geo's W, or one line where that would leave CUs without a block
-// (fewer than 256 blocks).  Nothing of a line's arithmetic depends on W.
+// Lines per block: Geo's W, or, where that would leave CUs without a block (fewer than 256
+// blocks), one line, but at least 40 threads: lines of 16 and 32 points have 10 or 20, and a
+// step of many such lines spends its time on the start of their blocks.  TS2 step in us with
+// one line / 40 / 80 threads / Geo's W: 16x16 complex64 10.8 / 10.1 / 10.3 / 12.1, 16x512 16.0 /
+// 13.4 / 13.5 / 15.2, 32^3 complex128 18.1 / 16.8 / 17.0 / 23.9, 16x16x128 18.9 / 15.3 / 15.4 /
+// 20.7 (Geo's W in an older build); 64 points (40 threads a line) 10.7 / - / 11.3 / 13.7.
+// Nothing of a line's arithmetic depends on W.
 template <typename T, int N, int E, int KIND>
 static hipError_t pass_n(cx<T>* psi, const PassArgs& a, hipStream_t st, const hipEvent_t* ev) {
-  constexpr int W = Geo<N, E>::W;
+  constexpr int W = Geo<N, E>::W, TL = Geo<N, E>::TL;
   if constexpr (W > 1) {
-    if (pass_blocks<W, KIND>(a) < 256) return pass_w<T, N, E, 1, KIND>(psi, a, st, ev);
+    if (pass_blocks<W, KIND>(a) < 256) return pass_w<T, N, E, (TL < 8 ? 8 / TL : 1), KIND>(psi, a, st, ev);
   }
   return pass_w<T, N, E, W, KIND>(psi, a, st, ev);
 }
