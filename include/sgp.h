@@ -108,7 +108,9 @@ int sgp_build_propagator(sgp_ctx* ctx, double tau, int scheme);
  * with N the exact nonlinear flow and L the exact linear flow.  Adjacent
  * nonlinear substeps of consecutive steps are merged (same clock value).
  * psi_dev: device pointer to the state (layout above), physical space on entry and
- * exit.  Asynchronous on the context stream; nsteps = 0 is a no-op. */
+ * exit.  Asynchronous on the context stream; nsteps = 0 is a no-op.  On a stream under
+ * capture the kernels go into the capture one by one; its replay repeats the call from the
+ * clock that the captured call started at. */
 int sgp_step(sgp_ctx* ctx, void* psi_dev, long nsteps);
 
 /* Observables of the state at the current clock (Sec. 2, discrete h^d sums):
@@ -329,7 +331,8 @@ int sgp_ensemble_set_workspace(sgp_ensemble* ens, void* dev_ptr, size_t bytes);
  * composition, Sec. 3.3, as for single grids).  SGP_ERR_ARG for another scheme. */
 int sgp_ensemble_build_propagator(sgp_ensemble* ens, double tau, int scheme);
 /* psi_devs: host array of n_inst device pointers (instance i: [ny][nx][5] complex).
- * Advances every instance by nsteps (common clock).  Asynchronous. */
+ * Advances every instance by nsteps (common clock).  Asynchronous.  SGP_ERR_STATE on a
+ * stream under capture (unless SGP_OPT_BATCHED is off). */
 int sgp_ensemble_step(sgp_ensemble* ens, void* const* psi_devs, long nsteps);
 /* SGP_OPT_GRAPH (default 1) as for contexts; SGP_OPT_BATCHED (default 1): 0 runs
  * every instance with its own launches (the unbatched reference). */

@@ -496,6 +496,12 @@ void drop_graph(sgp_ctx* c) {
   c->gpsi = nullptr;
 }
 
+// Whether the caller is capturing the stream.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return st && hipStreamIsCapturing(st, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 // The body graph of 2^k steps for state psi, captured if there is none.
 template <typename T>
 hipError_t get_graph(sgp_ctx* c, void* psi, int k) {
@@ -542,7 +548,9 @@ int step_impl(sgp_ctx* c, void* psi, long nsteps) {
   hipError_t e = run_xpass<T>(c, c->st, X_FIRST, psi, nl[0], CLOCK_ARG, c->t);
   if (e != hipSuccess) return hip_fail(c, e, "X-pass launch");
   long nbody = nsteps - 1;
-  const bool graph = c->use_graph && (psi == c->gpsi || psi == c->seen || nbody >= sgp_ctx::kGraphAtOnce || slab_body(c));
+  // (launched one by one into a caller's capture: a graph's launch is no part of it)
+  const bool graph = c->use_graph && !capturing(c->st) &&
+                     (psi == c->gpsi || psi == c->seen || nbody >= sgp_ctx::kGraphAtOnce || slab_body(c));
   c->seen = psi;
   if (graph && nbody > 0) {
     // the body steps replayed from graphs: nbody / 2^(L-1) replays of the largest,
@@ -2044,6 +2052,9 @@ int sgp_ensemble_step(sgp_ensemble* e, void* const* psi_devs, long nsteps) {
     e->t += nsteps * e->tau;
     return SGP_OK;
   }
+  // a first call copies its arguments from the host and waits, which a capture does not allow;
+  // later calls would be captured with a graph's launch, which is no part of it
+  if (capturing(e->st)) return efail(e, SGP_ERR_STATE, "batched ensemble steps cannot be captured into a graph");
   // the first X-pass of a call carries the current clock; the captured graph reads the
   // argument slots, so it holds for any state pointers
   e->psis.assign(psi_devs, psi_devs + e->n);
