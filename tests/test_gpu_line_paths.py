@@ -57,3 +57,27 @@ def test_steps_on_line_kernels_in_both_orders(dtype, shape, steps):
         err = rel_l2(Solver.from_device_layout(psi.cpu().numpy()), ref)
         print(f"  order {order}: rel l2 {err:.2e}", flush=True)
         assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,shape,slabs", [
+    ("complex64", (128, 64, 256), 2), ("complex64", (16, 512, 128), 16), ("complex128", (64, 128, 64), 4),
+])
+def test_slabs_on_line_kernels_change_nothing(dtype, shape, slabs):
+    """z-slabs launch the x- and y-line kernels on parts of the grid that start at plane z0
+    (one plane each at 16 slabs): the bits of whole passes."""
+    import torch
+    from paper_2603_25282_amd.sgp import Solver
+    psi0 = state(shape, 3)
+    print(f"case {slabs} slabs on line kernels {shape} {dtype}", flush=True)
+    out = []
+    for n in (0, slabs):
+        s = Solver(shape, L, PARAMS, dtype=dtype)
+        s.build_propagator(TAU, 4)
+        s.set_slabs(n)
+        psi = to_gpu(s, psi0)
+        s.time = 0.1
+        for steps in (4, 6):  # bodies of 3 and 5 steps
+            s.step(psi, steps)
+        torch.cuda.synchronize()
+        out.append(psi)
+    assert torch.equal(out[0], out[1])
