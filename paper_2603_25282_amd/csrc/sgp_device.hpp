@@ -320,7 +320,6 @@ struct Dft<8, SIGN, T> {
 // stride-8 accesses).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 3); }
-template <int N> struct LdsLine { static constexpr int size = N + N / 8; };
 
 // x * (wh + wl) with the small product folded in before the large one.
 template <typename T>
