@@ -261,14 +261,15 @@ int sgp_time_pass(sgp_ctx* ctx, void* psi_dev, int pass, int reps, double* avg_m
  *   adjoint) always uses order 0.
  * sgp_autotune: picks the fastest combination of the axes' widths (every
  *   combination, at most 9 in 2D and 27 in 3D, in 3D for both linear-substep
- *   orders; an axis whose pass of a step has a width of its own, see sgp_set_plan,
- *   keeps its plan) by timing `steps` steps of the
+ *   orders) by timing `steps` steps of the
  *   sgp_step path for each, after one untimed call of `steps` steps; psi_dev is
  *   a device state in the layout of sgp_step; it is advanced by every timed and
  *   untimed step (pass a scratch copy).  Needs the workspace and the propagator;
  *   the context time is left unchanged.  Writes the chosen widths to elems_out
  *   (0 for axes beyond dim) and, if ms_per_step is not NULL, the fastest time per
- *   step in ms.  The choice (and in 3D the split, read back with sgp_get_plan)
+ *   step in ms.  An axis whose pass of a step has a width of its own (see sgp_set_plan)
+ *   is not varied by this; it gets the width at which the observables pass along it is
+ *   fastest.  The choice (and in 3D the split, read back with sgp_get_plan)
  *   stays set on the context. */
 enum { SGP_PLAN_LINEAR = 3 };
 int sgp_plan_widths(int n, int dtype, int* out, int max_out);

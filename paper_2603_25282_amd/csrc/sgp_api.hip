@@ -723,6 +723,39 @@ int set_plan_impl(sgp_ctx* c, int axis, int e) {
   return SGP_OK;
 }
 
+// The observables pass along one axis; block partials to part.
+template <typename T>
+hipError_t launch_obs_axis(sgp_ctx* c, const void* psi, int axis, double* part) {
+  PassArgs a = base_args(c);
+  if (axis == 0) {
+    a.tw = c->at(c->off_tw[0]);
+    a.nu_scale_l = kPi / c->g.L[0];
+  } else {
+    column_geometry(c, axis, a);
+  }
+  a.s_arg = c->frame == SGP_FRAME_LAB ? 0.0 : c->t;  // lab frame: the trap at x
+  const int kind = axis == 0 ? OBS_X : (axis == 1 ? OBS_Y : OBS_Z);
+  return launch_obs<T>(kind, psi, a, c->g.n[axis], c->elems(axis), part, c->st);
+}
+
+// Milliseconds of the observables pass along one axis: the least of three launches, after an
+// untimed one.
+template <typename T>
+int time_obs_axis(sgp_ctx* c, const void* psi, int axis, hipEvent_t e0, hipEvent_t e1, double* ms) {
+  double* part = (double*)c->at(c->off_part);
+  for (int i = 0; i < 4; ++i) {
+    hipError_t e = hipEventRecord(e0, c->st);
+    if (e == hipSuccess) e = launch_obs_axis<T>(c, psi, axis, part);
+    if (e == hipSuccess) e = hipEventRecord(e1, c->st);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    float f = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&f, e0, e1);
+    if (e != hipSuccess) return hip_fail(c, e, "autotune timing");
+    if (i == 1 || (i > 1 && f < *ms)) *ms = f;
+  }
+  return SGP_OK;
+}
+
 // Autotuner: time `steps` whole steps (the sgp_step path, graphs included) for
 // every combination of the plan widths that the step uses (in 3D also both orders of
 // the linear substep) and keep the fastest.  psi is advanced by the timed steps; the context time
@@ -756,9 +789,8 @@ int autotune_impl(sgp_ctx* c, void* psi, int steps, int out_e[3], double* best_m
   double best = 0.0;
   int rc = time_steps(&best);
   std::vector<int> w[3];
-  // (an axis whose pass of a step runs on the line kernel keeps its width: the step does not
-  // use it, equal candidates would be told apart by noise, and the adjoint and observables
-  // passes would run at the winner's width)
+  // (an axis whose pass of a step runs on the line kernel keeps its width here: the step does
+  // not use it, and equal candidates would be told apart by noise)
   for (int ax = 0; ax < 3; ++ax)
     w[ax] = ax >= c->g.dim || c->line_e[ax] ? std::vector<int>{c->plan_e[ax]} : plan_widths(c->g.n[ax], (int)c->esize);
   int best_e[3] = {c->plan_e[0], c->plan_e[1], c->plan_e[2]};
@@ -787,6 +819,25 @@ int autotune_impl(sgp_ctx* c, void* psi, int steps, int out_e[3], double* best_m
         }
   for (int ax = 0; ax < c->g.dim && rc == SGP_OK; ++ax) rc = set_plan_impl<T>(c, ax, best_e[ax]);
   if (rc == SGP_OK && c->g.dim == 3) rc = set_plan_impl<T>(c, SGP_PLAN_LINEAR, best_ls);
+  // such an axis's width serves the observables and the adjoint.  It becomes the one that the
+  // observables pass runs fastest at (128^3 complex64: all passes at E = 8 412 us a call, with
+  // E = 16 along x 322, along y 360); the adjoint differs by a few percent, mostly likewise
+  // (329, 309 and 311 us a TS2 step).
+  for (int ax = 0; ax < c->g.dim && rc == SGP_OK; ++ax) {
+    if (!c->line_e[ax]) continue;
+    double least = 0.0;
+    for (int e : plan_widths(c->g.n[ax], (int)c->esize)) {
+      double ms = 0.0;
+      if (rc == SGP_OK) rc = set_plan_impl<T>(c, ax, e);
+      if (rc == SGP_OK) rc = time_obs_axis<T>(c, psi, ax, e0, e1, &ms);
+      if (rc != SGP_OK) break;
+      if (least == 0.0 || ms < least) {
+        least = ms;
+        best_e[ax] = e;
+      }
+    }
+    if (rc == SGP_OK) rc = set_plan_impl<T>(c, ax, best_e[ax]);
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   c->t = t_save;
@@ -812,16 +863,7 @@ int observables_impl(sgp_ctx* c, const void* psi, double out[12]) {
   double* red = (double*)c->at(c->off_red);
   double tot[3][NOBS];
   for (int axis = 0; axis < c->g.dim; ++axis) {
-    PassArgs a = base_args(c);
-    if (axis == 0) {
-      a.tw = c->at(c->off_tw[0]);
-      a.nu_scale_l = kPi / c->g.L[0];
-    } else {
-      column_geometry(c, axis, a);
-    }
-    a.s_arg = c->frame == SGP_FRAME_LAB ? 0.0 : c->t;  // lab frame: the trap at x
-    const int kind = axis == 0 ? OBS_X : (axis == 1 ? OBS_Y : OBS_Z);
-    hipError_t e = launch_obs<T>(kind, psi, a, c->g.n[axis], c->elems(axis), part, c->st);
+    hipError_t e = launch_obs_axis<T>(c, psi, axis, part);
     if (e != hipSuccess) return hip_fail(c, e, "observables launch");
     // block partials summed on the device in a fixed order (the next axis's launch
     // reuses the partials after this sum on the same stream)

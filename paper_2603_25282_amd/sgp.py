@@ -295,9 +295,9 @@ class Solver:
         return f"{arch}|{'x'.join(map(str, self.shape))}|{str(self.torch_dtype).replace('torch.', '')}|TS{scheme}"
 
     def autotune(self, psi, scheme, steps=20, cache=True):
-        """Pick the plan width of every axis that the step uses one on (sgp_autotune on
-        a scratch copy of psi; the other axes keep theirs)
-        and keep the choice in the JSON plan cache (plan_cache_path()); with cache,
+        """Pick the plan width of every axis (sgp_autotune on a scratch copy of psi: the
+        step's time decides, or the observables' along an axis whose pass of a step has a
+        width of its own) and keep the choice in the JSON plan cache (plan_cache_path()); with cache,
         a stored choice for this device, shape, dtype and scheme is applied without
         timing.  Returns (widths, ms_per_step or None)."""
         import json

@@ -7,27 +7,26 @@ from tests.gpu_util import to_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,shape,kept", [
-    ("complex64", (16, 512, 128), (0, 1)), ("complex64", (384, 16, 192), (0, 2)),
-    ("complex128", (64, 128, 64), (0, 1)), ("complex128", (256, 32, 64), (0, 2)),
-])
-def test_autotune_keeps_widths_that_the_step_does_not_use(dtype, shape, kept):
-    """The tuner times steps, so an axis whose pass has a width of its own keeps the width
-    that was set (for the adjoint and the observables), whatever it was."""
+@pytest.mark.parametrize("shape", [(16, 512, 128), (64, 64, 256), (32, 256, 256)])
+def test_autotune_of_an_axis_that_the_step_does_not_use(shape):
+    """The step runs the x-lines of these grids at a width of its own, so their plan serves
+    the observables and the adjoint.  The tuner times the observables for it, which at 16 are
+    a fifth faster than at any other width: it picks 16, whatever was set before."""
     import torch
     from paper_2603_25282_amd.sgp import Solver, plan_widths
     rng = np.random.default_rng(2)
     psi0 = rng.standard_normal((5,) + shape) + 1j * rng.standard_normal((5,) + shape)
-    s = Solver(shape, 8.0, (10.0, -1.0, 2.0, 0.5, 1.0, 1.0, 1.1, 1.2), dtype=dtype)
+    s = Solver(shape, 8.0, (10.0, -1.0, 2.0, 0.5, 1.0, 1.0, 1.1, 1.2), dtype="complex64")
     s.build_propagator(1e-3, 2)
     psi = to_gpu(s, psi0 / np.linalg.norm(psi0))
-    allowed = [plan_widths(n, dtype) for n in shape[::-1]]
-    for pick in (0, -1):
-        want = [w[pick] for w in allowed]
-        print(f"case autotune {shape} {dtype} from {want}", flush=True)
-        s.set_plan(want)
+    before = s.observables(psi)
+    allowed = [plan_widths(n, "complex64") for n in shape[::-1]]
+    for start in ([4, 0, 0], [8, 0, 0]):
+        s.set_plan(start)
         widths, ms = s.autotune(psi, 2, steps=2, cache=False)
-        assert ms > 0 and widths == s.get_plan()
-        for ax in range(3):
-            assert widths[ax] == want[ax] if ax in kept else widths[ax] in allowed[ax]
+        print(f"case autotune {shape} from {start}: {widths}", flush=True)
+        assert ms > 0 and widths == s.get_plan() and widths[3] in (0, 1)
+        assert widths[0] == 16 and all(w in a for w, a in zip(widths, allowed))
+        assert s.time == 0.0
     torch.cuda.synchronize()
+    assert np.allclose(s.observables(psi), before, rtol=2e-6, atol=2e-6)
