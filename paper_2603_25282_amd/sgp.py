@@ -234,7 +234,8 @@ class Solver:
         return dict(zip(keys, out[:]))
 
     def time_pass(self, psi, pass_kind, reps, in_step=False, in_steps=False):
-        """Average milliseconds of one pass (0 X, 1 Y, 2 Z, 3 inverse Y), timed with
+        """Average milliseconds of one pass (0 X, 1 Y, 2 Z, 3 the one with the inverse
+        transform along y, which is Y), timed with
         HIP events on the library's stream: reps launches back to back; (in_step)
         reps rounds of one substep's passes in step order; or (in_steps) every launch
         of the pass inside reps whole steps of the step schedule, each launch timed
@@ -271,8 +272,8 @@ class Solver:
 
     def get_plan(self):
         """Plan width E of the passes along x, y (, z); in 3D a fourth entry, the
-        linear substep's split (SGP_PLAN_LINEAR: 0 = the in-plane part in the y-pass,
-        then the z kinetic phase in the z-pass; 1 = the z-pass first)."""
+        order of the linear substep's passes (SGP_PLAN_LINEAR: 0 = the in-plane part in
+        the y-pass, then the z kinetic phase in the z-pass; 1 = the z-pass first)."""
         e = ctypes.c_int()
         out = []
         for ax in range(len(self.shape)) if len(self.shape) == 2 else (0, 1, 2, SGP_PLAN_LINEAR):
@@ -282,7 +283,7 @@ class Solver:
 
     def set_plan(self, widths):
         """Plan widths per axis (x, y (, z)); 0 = default; in 3D an optional fourth
-        entry sets the linear substep's split (see get_plan)."""
+        entry sets the order of the linear substep's passes (see get_plan)."""
         if len(widths) > len(self.shape) + (1 if len(self.shape) == 3 else 0):
             raise SgpError(f"plan {list(widths)} has too many entries for a {len(self.shape)}D grid")
         for ax, e in enumerate(widths):
